@@ -88,11 +88,11 @@ __device__ inline void from_modal(const Modes& md, double xh, const double xm[5]
 // v = Xi (yT - N wdg) for a plastic point (modal), returns wdg and w_a
 __device__ inline void reverse_plastic(const Modes& md, const Local& loc, double yh, const double ym[5], double ya,
                                        double ydg, double& vh, double vm[5], double& wdg, double& wa) {
-    const double lam = loc.lam, om = 1.0 / (1.0 - lam * loc.svar);
+    const double lam = loc.lam, om = recip(1.0 - lam * loc.svar);
     double my = 0.0;
 #pragma unroll
     for (int i = 0; i < 5; ++i) my += loc.mvec[i] * ym[i];
-    wdg = (my * om - ya - ydg) / (loc.svar * om + loc.dsig);
+    wdg = (my * om - ya - ydg) * recip(loc.svar * om + loc.dsig);
     wa = ya + loc.dsig * wdg;
     double z[5], mz = 0.0;
 #pragma unroll
@@ -103,7 +103,7 @@ __device__ inline void reverse_plastic(const Modes& md, const Local& loc, double
     vh = md.k3 * yh;
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
-        const double ai = md.mu2 / (1.0 + md.mu2 * lam * md.eta[i]);
+        const double ai = md.mu2 * recip(1.0 + md.mu2 * lam * md.eta[i]);
         vm[i] = ai * z[i] + lam * loc.mvec[i] * mz * om;
     }
 }
@@ -148,8 +148,7 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
     double M[3][3], Q[3][3], mu_c[3], eh[3];
     cauchy_green_minus_identity<double>(H, M);
     eig_sym3<double>(M, mu_c, Q);
-#pragma unroll
-    for (int p = 0; p < 3; ++p) eh[p] = 0.5 * log1p(mu_c[p]);
+    half_logs(mu_c, eh);
     double eps[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -166,10 +165,7 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
 #pragma unroll
         for (int p = 0; p < 3; ++p) fh[i][p] = Q[i][p] + (H[i][0] * Q[0][p] + H[i][1] * Q[1][p] + H[i][2] * Q[2][p]);
     double f1[3][3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int r = 0; r < 3; ++r) f1[p][r] = (p == r) ? 0.5 / (1.0 + mu_c[p]) : dd1<double>(mu_c[p], mu_c[r], eh[p], eh[r]);
+    divided_f1(mu_c, eh, f1);
     __syncthreads();
 
     // ---- local update (material frame with an orientation)
@@ -181,9 +177,9 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
         rotate_sym<true>(Th, hn, 1.0);
     }
     Modes md;
-    hill_modes(mat, md);
+    hill_modes<true>(mat, md);
     Local loc;
-    local_update(eps, hn, mat, md, loc);
+    local_update<true>(eps, hn, mat, md, loc);
 
     // ---- output cotangents: Tbar = w detJ0 P_L : sym(Fbar^T Lambda) (Cartesian
     // Mandel), ebar (Mandel) and abar from mu
@@ -226,14 +222,14 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
         to_modal(md, eb, ebh, ebm);
         double vh, vm[5], vh_mu, vm_mu[5];
         if (loc.plastic) {
-            const double dg = loc.dgamma, phi = loc.phi;
+            const double dg = loc.dgamma, iphi = recip(loc.phi);
             double NE = 0.0;
 #pragma unroll
             for (int i = 0; i < 5; ++i) NE += loc.Nm[i] * ebm[i];
             double yT[5], yTmu[5];
 #pragma unroll
             for (int i = 0; i < 5; ++i) {
-                const double dNe = (md.eta[i] * ebm[i] - loc.Nm[i] * NE) / phi;  // dN/dT ebar
+                const double dNe = (md.eta[i] * ebm[i] - loc.Nm[i] * NE) * iphi;  // dN/dT ebar
                 yTmu[i] = dg * dNe;
                 yT[i] = tbm[i] + yTmu[i];
             }
@@ -261,8 +257,8 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
                 double vh_ = 0.0;
 #pragma unroll
                 for (int c = 0; c < 6; ++c) vh_ += vmE[c] * hv[k][c];
-                const double dphi = tht[k] / (2.0 * phi);
-                const double vNt = vh_ / phi - vN * dphi / phi;
+                const double dphi = 0.5 * tht[k] * iphi;
+                const double vNt = (vh_ - vN * dphi) * iphi;
                 th_bar[k] = -dg * vNt - wdg * dphi;
             }
             // hardening parameters at alpha_{n+1}
@@ -274,7 +270,7 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
                 d1 = 1.0 - ex;
                 d2 = mat.eps0 * alpha * ex;
             } else {
-                d0 = loc.sig / mat.K;
+                d0 = loc.sig * recip(mat.K);
                 d1 = loc.dsig;
                 d2 = loc.sig * log(mat.eps0 + alpha);
             }
@@ -332,7 +328,12 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
                            fh[i][2] * 2.0 * f1[2][p] * Yh[2][p];
     }
     double sg = 0.0;
+    double fc[3][3];  // f^_bs / c_s, as f1(c, c) = 1 / (2 c)
     if constexpr (FBAR) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int s2 = 0; s2 < 3; ++s2) fc[b][s2] = fh[b][s2] * (2.0 * f1[s2][s2]);
         // F-bar: ubar_Jb = sum_g beta (Xf grad N_J)_b + sg (qbar_Jb - q_g,Jb),
         // sg = (Xf : Fbar) / 3, q_g = beta g^ (f^/c)^T, qbar = sum_g cw q_g
 #pragma unroll
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
             for (int b = 0; b < 3; ++b) {
                 double x = 0.0;
 #pragma unroll
-                for (int s2 = 0; s2 < 3; ++s2) x += sG[slot][gp][3 * J + s2] * fh[b][s2] / (1.0 + mu_c[s2]);
+                for (int s2 = 0; s2 < 3; ++s2) x += sG[slot][gp][3 * J + s2] * fc[b][s2];
                 red[3 * J + b][tid] = cw * beta * x;
             }
         __syncthreads();
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
             if constexpr (FBAR) {
                 double qg = 0.0;
 #pragma unroll
-                for (int s2 = 0; s2 < 3; ++s2) qg += sG[slot][gp][3 * J + s2] * fh[b][s2] / (1.0 + mu_c[s2]);
+                for (int s2 = 0; s2 < 3; ++s2) qg += sG[slot][gp][3 * J + s2] * fc[b][s2];
                 x = beta * x - sg * beta * qg;
             }
             red[3 * J + b][tid] = x;

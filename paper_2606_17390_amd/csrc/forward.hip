@@ -161,8 +161,7 @@ __device__ inline void kin_and_log(const double (*nd)[W], int gp, GP<R>& s, doub
     R M[3][3];
     cauchy_green_minus_identity<R>(s.H, M);
     eig_sym3<R>(M, s.mu, s.Q);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) s.eh[a] = R(0.5) * m_log1p(s.mu[a]);
+    half_logs(s.mu, s.eh);
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         const int i = mi(k), j = mj(k);
@@ -294,7 +293,7 @@ void fwd_kernel(const FwdArgs a) {
             rotate_sym<true>(Th, hn, 1.0);
         }
         Modes md;
-        hill_modes(mat, md);
+        hill_modes<std::is_same<R, double>::value>(mat, md);
         Local loc;
         if constexpr (BARLAT) {
             BarlatCoef bco;
@@ -310,7 +309,7 @@ void fwd_kernel(const FwdArgs a) {
             loc.ftr = lb.ftr;
             loc.sy_n = lb.sy_n;
         } else {
-            local_update(eps, hn, mat, md, loc);
+            local_update<std::is_same<R, double>::value>(eps, hn, mat, md, loc);
         }
         if constexpr (ORIENT) {
             double Th[3][3];
@@ -364,14 +363,7 @@ void fwd_kernel(const FwdArgs a) {
             mandel_to_frame<R>(s.Q, Tm, Th);
         }
         R f1[3][3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-            for (int r = p; r < 3; ++r) {
-                const R v = (p == r) ? R(0.5) / (R(1) + s.mu[p]) : dd1<R>(s.mu[p], s.mu[r], s.eh[p], s.eh[r]);
-                f1[p][r] = v;
-                f1[r][p] = v;
-            }
+        divided_f1(s.mu, s.eh, f1);
         R Sh[3][3];
 #pragma unroll
         for (int p = 0; p < 3; ++p)
@@ -511,23 +503,7 @@ void fwd_kernel(const FwdArgs a) {
             }
             // ---- second divided differences f2(c_a, c_b, c_r)
             R f2[3][3][3];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                const R cp = R(1) + s.mu[p];
-                f2[p][p][p] = R(-0.25) / (cp * cp);
-            }
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int r = 0; r < 3; ++r)
-                    if (r != p) {
-                        const R v = dd2_pair<R>(s.mu[p], s.mu[r], s.eh[p], s.eh[r]);
-                        f2[p][p][r] = f2[p][r][p] = f2[r][p][p] = v;
-                    }
-            {
-                const R v = dd2_triple<R>(s.mu[0], s.mu[1], s.mu[2], s.eh[0], s.eh[1], s.eh[2]);
-                f2[0][1][2] = f2[0][2][1] = f2[1][0][2] = f2[1][2][0] = f2[2][0][1] = f2[2][1][0] = v;
-            }
+            divided_f2(s.mu, s.eh, f1, f2);
             // ---- Lagrangian tangent (Mandel, eigenframe):
             //      Cm = P^ Ch P^ + L,  P^_I = 2 f1(I),  (L:dC)_ab = 4 sum_r f2_abr (dC_ar T_rb + T_ar dC_rb)
             R Cm[6][6];
@@ -542,14 +518,11 @@ void fwd_kernel(const FwdArgs a) {
                     R x = R(0);
 #pragma unroll
                     for (int t = 0; t < 3; ++t) {
-                        R Ept = R(0), Etr = R(0);
-                        if ((p == c && t == d) || (p == d && t == c)) Ept = ev;
-                        if ((t == c && r == d) || (t == d && r == c)) Etr = ev;
-                        if (c == d) {
-                            Ept = (p == c && t == c) ? R(1) : R(0);
-                            Etr = (t == c && r == c) ? R(1) : R(0);
-                        }
-                        x += f2[p][r][t] * (Ept * Th[t][r] + Th[p][t] * Etr);
+                        // most entries of E_J are zero: only the others are formed
+                        const bool pt = (p == c && t == d) || (p == d && t == c);
+                        const bool tr = (t == c && r == d) || (t == d && r == c);
+                        if (pt) x += f2[p][r][t] * (ev * Th[t][r]);
+                        if (tr) x += f2[p][r][t] * (Th[p][t] * ev);
                     }
                     const R Pi = R(2) * f1[p][r], Pj = R(2) * f1[c][d];
                     Cm[I][J] = Pi * Ch[I][J] * Pj + R(4) * mw<R>(I) * x;
@@ -597,7 +570,7 @@ void fwd_kernel(const FwdArgs a) {
                     for (int p = 0; p < 3; ++p) {
                         Yh[i][p] = fh[i][0] * (Sh[0][p] + Wm[0][p]) + fh[i][1] * (Sh[1][p] + Wm[1][p]) +
                                    fh[i][2] * (Sh[2][p] + Wm[2][p]);
-                        fc[i][p] = fh[i][p] / (R(1) + s.mu[p]);
+                        fc[i][p] = fh[i][p] * (R(2) * f1[p][p]);  // f1(c, c) = 1 / (2 c)
                     }
             }
             // element sums Ubar (row gp) and qbar through the hand-off area, in

@@ -116,8 +116,7 @@ __device__ inline void kin_log_v(const double (*nd)[9], int gp, GPv<R>& s, doubl
     R M[3][3];
     cauchy_green_minus_identity<R>(s.H, M);
     eig_sym3<R>(M, s.mu, s.Q);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) s.eh[a] = R(0.5) * m_log1p(s.mu[a]);
+    half_logs(s.mu, s.eh);
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         const int i = mi(k), j = mj(k);
@@ -203,9 +202,9 @@ void vjp_kernel(const VjpArgs a) {
             rotate_sym<true>(Th, hn, 1.0);
         }
         Modes md;
-        hill_modes(mat, md);
+        hill_modes<true>(mat, md);
         Local loc;
-        local_update(eps, hn, mat, md, loc);
+        local_update<true>(eps, hn, mat, md, loc);
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int i = 0; i < 3; ++i)
@@ -242,15 +241,15 @@ void vjp_kernel(const VjpArgs a) {
 #pragma unroll
                 for (int p = 0; p < 3; ++p)
                     fh[i][p] = s.Q[i][p] + (s.H[i][0] * s.Q[0][p] + s.H[i][1] * s.Q[1][p] + s.H[i][2] * s.Q[2][p]);
-            R Tb[3][3];
+            R Tb[3][3], f1[3][3];
+            divided_f1(s.mu, s.eh, f1);
 #pragma unroll
             for (int p = 0; p < 3; ++p)
 #pragma unroll
                 for (int r = p; r < 3; ++r) {
                     R x = R(0.5) * (fh[0][p] * Lh[0][r] + fh[1][p] * Lh[1][r] + fh[2][p] * Lh[2][r] +
                                     fh[0][r] * Lh[0][p] + fh[1][r] * Lh[1][p] + fh[2][r] * Lh[2][p]);
-                    const R f1 = (p == r) ? R(0.5) / (R(1) + s.mu[p]) : dd1<R>(s.mu[p], s.mu[r], s.eh[p], s.eh[r]);
-                    Tb[p][r] = Tb[r][p] = R(2) * f1 * x;
+                    Tb[p][r] = Tb[r][p] = R(2) * f1[p][r] * x;
                 }
             R tbm[6];
             frame_to_mandel<R>(s.Q, Tb, tbm);
@@ -265,7 +264,7 @@ void vjp_kernel(const VjpArgs a) {
 
             // ---- reverse-mode adjoint of the local update (double)
             const double lam = loc.lam, dg = loc.dgamma, phi = loc.phi, sv = loc.svar;
-            const double om = 1.0 / (1.0 - lam * sv);
+            const double om = recip(1.0 - lam * sv), iphi = recip(phi);
             double tmod[5];
             const double tbh = (tb[0] + tb[1] + tb[2]) * kInvSqrt3;
             tmod[0] = md.v1[0] * tb[0] + md.v1[1] * tb[1] + md.v1[2] * tb[2];
@@ -279,14 +278,14 @@ void vjp_kernel(const VjpArgs a) {
             double u[5], xin[5], uN = 0.0;
 #pragma unroll
             for (int i = 0; i < 5; ++i) {
-                const double ai = md.mu2 / (1.0 + md.mu2 * lam * md.eta[i]);
+                const double ai = md.mu2 * recip(1.0 + md.mu2 * lam * md.eta[i]);
                 u[i] = ai * tmod[i] + lam * loc.mvec[i] * mT * om;
                 xin[i] = loc.mvec[i] * om;
                 uN += u[i] * loc.Nm[i];
             }
             const double uh = md.k3 * tbh;
             const double Dn = sv * om + loc.dsig;
-            const double xN = sv * om;
+            const double xN = sv * om, uD = uN * recip(Dn);
             // Cartesian Mandel of u and Xi N
             double uc[6], xc[6];
 #pragma unroll
@@ -312,10 +311,10 @@ void vjp_kernel(const VjpArgs a) {
                     uh_ += uc[c] * hv[k][c];
                     xh_ += xc[c] * hv[k][c];
                 }
-                const double dphi = tht[k] / (2.0 * phi);
-                const double uNt = uh_ / phi - uN * dphi / phi;
-                const double xNt = xh_ / phi - xN * dphi / phi;
-                gbar[k] = -dg * uNt - (uN / Dn) * (-dg * xNt + dphi);
+                const double dphi = 0.5 * tht[k] * iphi;
+                const double uNt = (uh_ - uN * dphi) * iphi;
+                const double xNt = (xh_ - xN * dphi) * iphi;
+                gbar[k] = -dg * uNt - uD * (-dg * xNt + dphi);
             }
             // hardening parameters at alpha_{n+1}: Swift (K, eps0, n) or Voce (sig0, Q, b)
             const double alpha = loc.hist[6];
@@ -326,13 +325,13 @@ void vjp_kernel(const VjpArgs a) {
                 d1 = 1.0 - ex;
                 d2 = mat.eps0 * alpha * ex;
             } else {
-                d0 = loc.sig / mat.K;
+                d0 = loc.sig * recip(mat.K);
                 d1 = loc.dsig;
                 d2 = loc.sig * log(mat.eps0 + alpha);
             }
-            gbar[4] = (uN / Dn) * d0;
-            gbar[5] = (uN / Dn) * d1;
-            gbar[6] = (uN / Dn) * d2;
+            gbar[4] = uD * d0;
+            gbar[5] = uD * d1;
+            gbar[6] = uD * d2;
             const double w = (double)s.detJ;
 #pragma unroll
             for (int k = 0; k < 7; ++k) gbar[k] *= w;
