@@ -37,6 +37,21 @@ constexpr int kLanes = 32;                       // lanes per node of the block 
 constexpr int kDenseMax = 3 * FEM_AMG_DENSE_NODES;  // dofs of a dense coarsest level
 constexpr double kStall = 0.85;                  // stop when a level keeps more nodes than this
 constexpr int kPostGrid = 2048;                  // workgroup cap of the persistent level products
+// The prolongation is folded into the post-smoothing product on levels of at
+// most this many nodes: a launch costs 4.8 us there (its few dependent loads,
+// not work) and the folded gather about 1 us.  On the finest level of 10^6
+// nodes the extra gather per block cost more than the pass it saves (367
+// against 325 ms for a solve).
+constexpr int32_t kFuseNodes = 32768;
+// A consumer of a K-step's workgroup partials forms the step's coefficients
+// itself in every workgroup, in the same fixed order, instead of waiting for
+// a one-workgroup kernel (4.8 us), while all its workgroups together read at
+// most this many partials (16 MB or less, about 3 us from L2).
+constexpr int64_t kFusePartials = 1 << 20;
+constexpr int kSeg = 4;                          // blocks per segment of the packed tail
+constexpr int kTailThreads = 1024;
+constexpr int kTailSeg0 = 2 * kTailThreads;      // segments of the tail's first level (two per thread)
+constexpr size_t kTailLds = 160 * 1024;
 
 struct Level {
     int32_t n = 0;           // nodes
@@ -58,6 +73,15 @@ struct Level {
     int32_t* gdst = nullptr;   // [nb] entry offset of the coarse block's (0,0) entry
     uint16_t* gdlen = nullptr; // [nb] row length of the coarse block's rows
     uint8_t* gfix = nullptr;   // [nb] bit a: identity on row a (diagonal block, no free fine dof)
+    int32_t* aggm = nullptr;   // [n_fine] aggregate | free dofs << 28, where post_prolong_kernel reads it
+    // packed tail form (levels of the tail, see tail_packed_kernel)
+    int32_t ns = 0;            // segments of up to kSeg blocks of one row
+    float* pv = nullptr;       // [kSeg][9][ns] values
+    uint64_t* pc = nullptr;    // [ns] node columns, 16 bits each
+    int32_t* psrc = nullptr;   // [kSeg][ns] entry offset of the block's (0,0) entry in vals, -1 = none
+    int32_t* plen = nullptr;   // [ns] row length
+    int4* prow = nullptr;      // [n] first segment, segments, aggregate, free dofs | members << 8
+    uint4* pmem = nullptr;     // [n] members in the level above, 16 bits each
     // K-cycle steps on this level (levels >= 1)
     double* kc1 = nullptr;     // [3 n] first cycle result c1
     double* kv1 = nullptr;     // [3 n] A c1
@@ -66,6 +90,33 @@ struct Level {
 };
 
 }  // namespace
+
+namespace fem {
+namespace {
+// arguments of tail_packed_kernel
+struct TailPackedLevel {
+    int32_t n, ns;
+    int32_t own;   // first thread owning a row of the level
+    int32_t x;     // offset of the level's vector in LDS (doubles)
+    int32_t v;     // offset of its packed values in LDS (levels after the first)
+    const float* pv;
+    const uint64_t* pc;
+    const int4* row;
+    const uint4* mem;
+    const double* minv;
+};
+
+struct TailPacked {
+    int nlv, dense, nd;
+    // LDS offsets (doubles): segment sums, residual; the smoother blocks of
+    // all rows and the coarsest inverse (-1: read from memory)
+    int oC, oR, oM, oI;
+    const double *cinv, *b, *x;
+    double* y;
+    TailPackedLevel L[FEM_AMG_MAX_LEVELS];
+};
+}  // namespace
+}  // namespace fem
 
 struct fem_amg {
     int device = 0;
@@ -86,6 +137,9 @@ struct fem_amg {
     bool updated = false;
     fem_amg_cycle cycle = FEM_AMG_CYCLE_V;
     int32_t kmin = 0;          // K-cycle steps on levels of at least this many nodes
+    bool packed = false;       // the tail runs from its packed form
+    fem::TailPacked* tail = nullptr;  // device: its arguments
+    size_t tail_lds = 0;       // bytes of LDS it takes
 };
 
 namespace fem {
@@ -539,6 +593,246 @@ __global__ __launch_bounds__(1024) void tail_kernel(TailArgs A, const int32_t* f
     }
 }
 
+// The same part of the cycle from a packed form.  tail_kernel spends its time
+// on chains of dependent loads that miss the caches (row offsets, column,
+// vector entry, for every round of every sweep; caches do not survive from
+// one kernel to the next): 26 us for 266 + 36 + 6 nodes.  Here every operator
+// entry is requested at the start, all at once: the first level's values go
+// to registers, the smaller levels', the coarsest inverse and all vectors to
+// LDS, and the sweeps then touch LDS only.  Values are packed by segments of
+// up to kSeg blocks of one row, one thread per segment: it leaves its three
+// partial sums in LDS, and the thread that owns the row adds the row's
+// segments in order and holds its right-hand side.  Levels that do not fit (more than 2048 segments on the
+// first level, more than 160 KB of LDS in all) take tail_kernel.
+// one segment: 9 kSeg values at v[q * stride], node columns in c
+__device__ __forceinline__ void tail_segment(const float* v, int stride, uint64_t c, const double* __restrict__ X,
+                                             double* __restrict__ out) {
+    double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < kSeg; ++j) {
+        const int J = 3 * (int)((c >> (16 * j)) & 0xffffu);
+        const double x0 = X[J], x1 = X[J + 1], x2 = X[J + 2];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            s[a] += (double)v[(9 * j + 3 * a) * stride] * x0 + (double)v[(9 * j + 3 * a + 1) * stride] * x1 +
+                    (double)v[(9 * j + 3 * a + 2) * stride] * x2;
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) out[a] = s[a];
+}
+
+// r = b - (sum of the segments g0, ..., g0 + ng - 1)
+__device__ __forceinline__ void tail_residual(const double* __restrict__ C, int g0, int ng, const double b[3],
+                                              double r[3]) {
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int g = g0; g < g0 + ng; ++g)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) s[a] += C[3 * g + a];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) r[a] = b[a] - s[a];
+}
+
+__device__ __forceinline__ void tail_smooth(const double* m, const double r[3], double o[3]) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) o[a] = m[3 * a] * r[0] + m[3 * a + 1] * r[1] + m[3 * a + 2] * r[2];
+}
+
+__global__ __launch_bounds__(kTailThreads) void tail_packed_kernel(const TailPacked* __restrict__ P,
+                                                                   const int32_t* __restrict__ fl) {
+    if (stopped(fl)) return;
+    extern __shared__ double sm[];
+    const int tid = (int)threadIdx.x;
+    const int nlv = P->nlv, nop = P->dense ? nlv - 1 : nlv;  // levels with an operator
+    double* __restrict__ C = sm + P->oC;
+    double* __restrict__ sr = sm + P->oR;
+    double* __restrict__ X0 = sm + P->L[0].x;
+    const int ns0 = P->L[0].ns;
+    // ---- everything that does not change, requested at once
+    float v0[2][9 * kSeg];
+    uint64_t c0[2] = {0, 0};
+    if (nop > 0) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int g = min(tid + k * kTailThreads, ns0 - 1);  // past the end: the last one again, not used
+            const char* p = reinterpret_cast<const char*>(P->L[0].pv);
+            const uint32_t at = 4u * (uint32_t)g;
+#pragma unroll
+            for (int q = 0; q < 9 * kSeg; ++q, p += 4 * (size_t)ns0) v0[k][q] = *reinterpret_cast<const float*>(p + at);
+            c0[k] = P->L[0].pc[g];
+        }
+    }
+    int lev = -1, row = 0;
+    int4 ri = make_int4(0, 0, 0, 0);
+    uint4 mb = make_uint4(0, 0, 0, 0);
+    double b[3] = {0.0, 0.0, 0.0};
+    const double* m = nullptr;  // smoother block of the own row
+    const int oM = P->oM;
+    for (int l = 0; l < nlv; ++l) {
+        const int r = tid - P->L[l].own, n = P->L[l].n;
+        const double* minv = P->L[l].minv;
+        if (r >= 0 && r < n) {
+            lev = l;
+            row = r;
+            ri = P->L[l].row[r];
+            if (l > 0) mb = P->L[l].mem[r];
+            m = minv + 9 * r;
+        }
+        if (oM >= 0 && l < nop)
+            for (int i = tid; i < 9 * n; i += kTailThreads) sm[oM + 9 * P->L[l].own + i] = minv[i];
+    }
+    if (oM >= 0) m = sm + oM + 9 * tid;
+    if (lev == 0) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            b[a] = P->b[3 * row + a];
+            X0[3 * row + a] = nop > 0 ? P->x[3 * row + a] : b[a];
+        }
+    }
+    for (int l = 1; l < nop; ++l) {
+        const int ns = P->L[l].ns;
+        const float* pv = P->L[l].pv;
+        const uint64_t* pc = P->L[l].pc;
+        float* dv = reinterpret_cast<float*>(sm + P->L[l].v);
+        uint64_t* dc = reinterpret_cast<uint64_t*>(dv + 9 * kSeg * ns);
+        for (int i = tid; i < 9 * kSeg * ns; i += kTailThreads) dv[i] = pv[i];
+        for (int i = tid; i < ns; i += kTailThreads) dc[i] = pc[i];
+    }
+    const int nd = P->nd, oI = P->oI;
+    const double* __restrict__ cinv = P->cinv;
+    if (oI >= 0)
+        for (int i = tid; i < nd * nd; i += kTailThreads) sm[oI + i] = cinv[i];
+    __syncthreads();
+
+    // ---- down: the residual of level l - 1 restricted to level l, whose
+    // first sweep (or, for the coarsest inverse, right-hand side) goes to its
+    // vector; the segments of level l - 1 come from registers (l = 1) or LDS
+    for (int l = 1; l < nlv; ++l) {
+        if (l == 1) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int g = tid + k * kTailThreads;
+                if (g < ns0) tail_segment(v0[k], 1, c0[k], X0, C + 3 * g);
+            }
+        } else {
+            const int ns = P->L[l - 1].ns;
+            const double* X = sm + P->L[l - 1].x;
+            const float* dv = reinterpret_cast<const float*>(sm + P->L[l - 1].v);
+            const uint64_t* dc = reinterpret_cast<const uint64_t*>(dv + 9 * kSeg * ns);
+            for (int g = tid; g < ns; g += kTailThreads) tail_segment(dv + g, ns, dc[g], X, C + 3 * g);
+        }
+        __syncthreads();
+        if (lev == l - 1) {
+            double r[3];
+            tail_residual(C, ri.x, ri.y, b, r);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) sr[3 * row + a] = ((ri.w >> a) & 1) ? r[a] : 0.0;
+        }
+        __syncthreads();
+        if (lev == l) {
+            const uint32_t w[4] = {mb.x, mb.y, mb.z, mb.w};
+            const int cnt = ri.w >> 8;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k < cnt) {
+                    const int i = (int)((w[k >> 1] >> (16 * (k & 1))) & 0xffffu);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) b[a] += sr[3 * i + a];
+                }
+            double* X = sm + P->L[l].x;
+            double d[3] = {b[0], b[1], b[2]};
+            if (l < nop) tail_smooth(m, b, d);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) X[3 * row + a] = d[a];
+        }
+        __syncthreads();
+    }
+    if (P->dense) {
+        // coarsest level x = Cinv b, 8 lanes per row (at most 96 rows)
+        double* X = sm + P->L[nlv - 1].x;
+        const int i = tid >> 3;
+        double s = 0.0;
+        if (i < nd) {
+            if (oI >= 0) {
+                const double* ci = sm + oI + i * nd;
+                for (int j = tid & 7; j < nd; j += 8) s += ci[j] * X[j];
+            } else {
+                const double* __restrict__ ci = cinv + i * nd;
+                for (int j = tid & 7; j < nd; j += 8) s += ci[j] * X[j];
+            }
+        }
+#pragma unroll
+        for (int k = 1; k < 8; k <<= 1) s += __shfl_xor(s, k, 8);
+        __syncthreads();
+        if (i < nd && (tid & 7) == 0) X[i] = s;
+        __syncthreads();
+    }
+    // ---- up: prolongation (but on the coarsest level) and second sweep,
+    // x + M (b - A x) in place; the first level follows the loop
+    for (int l = nop - 1; l >= 0; --l) {
+        double* X = sm + P->L[l].x;
+        if (l + 1 < nlv) {
+            if (lev == l) {
+                const double* Y = sm + P->L[l + 1].x;
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    if ((ri.w >> a) & 1) X[3 * row + a] += Y[3 * ri.z + a];
+            }
+            __syncthreads();
+        }
+        if (l == 0) break;
+        const int ns = P->L[l].ns;
+        const float* dv = reinterpret_cast<const float*>(sm + P->L[l].v);
+        const uint64_t* dc = reinterpret_cast<const uint64_t*>(dv + 9 * kSeg * ns);
+        for (int g = tid; g < ns; g += kTailThreads) tail_segment(dv + g, ns, dc[g], X, C + 3 * g);
+        __syncthreads();
+        if (lev == l) {
+            double r[3], d[3];
+            tail_residual(C, ri.x, ri.y, b, r);
+            tail_smooth(m, r, d);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) X[3 * row + a] += d[a];
+        }
+        __syncthreads();
+    }
+    if (nop > 0) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            // opaque to the compiler, which would keep the values of the first
+            // sweep converted to double until here (144 registers)
+#pragma unroll
+            for (int q = 0; q < 9 * kSeg; ++q) asm volatile("" : "+v"(v0[k][q]));
+            const int g = tid + k * kTailThreads;
+            if (g < ns0) tail_segment(v0[k], 1, c0[k], X0, C + 3 * g);
+        }
+        __syncthreads();
+    }
+    if (lev == 0) {
+        double* __restrict__ y = P->y;
+        double d[3] = {0.0, 0.0, 0.0};
+        if (nop > 0) {
+            double r[3];
+            tail_residual(C, ri.x, ri.y, b, r);
+            tail_smooth(m, r, d);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) y[3 * row + a] = X0[3 * row + a] + d[a];
+    }
+}
+
+// packed values of a tail level (once per fem_amg_update)
+__global__ __launch_bounds__(256) void tail_pack_kernel(int32_t ns, const int32_t* __restrict__ psrc,
+                                                        const int32_t* __restrict__ plen,
+                                                        const float* __restrict__ vals, float* __restrict__ pv) {
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i >= kSeg * ns) return;
+    const int j = i / ns, g = i - j * ns;
+    const int32_t off = psrc[i], len = plen[g];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) pv[(9 * j + 3 * a + c) * ns + g] = off >= 0 ? vals[off + a * len + c] : 0.0f;
+}
+
 // Dense coarsest level (one workgroup): x = Cinv b with b = P^T r (mptr
 // given) or b = r (mptr NULL: the finest level is the dense one)
 __global__ __launch_bounds__(256) void dense_apply_kernel(int32_t n, const int32_t* __restrict__ mptr,
@@ -759,43 +1053,68 @@ __global__ __launch_bounds__(256) void kstep_product(int32_t n, const int32_t* _
     }
 }
 
-// One workgroup: the sums of the np workgroup partials (fixed order), then
-// STEP 1: ksc[0] = (v1, v1), ksc[1] = a1;  STEP 2: ksc[2] = a1 - a2 g,
-// ksc[3] = a2 (zero where a denominator is not positive)
+// The sums of the np workgroup partials (fixed order, every thread of a
+// 256-thread workgroup gets them), then STEP 1: o = (v1, v1), a1;
+// STEP 2: o = a1 - a2 g, a2 (zero where a denominator is not positive)
 template <int STEP>
-__global__ __launch_bounds__(256) void kstep_scalars(int np, const double* __restrict__ part, double* __restrict__ ksc,
-                                                     const int32_t* __restrict__ fl) {
-    if (stopped(fl)) return;
+__device__ inline void kstep_coefficients(int np, const double* __restrict__ part, const double* __restrict__ ksc,
+                                          double o[2]) {
     double q0 = 0.0, q1 = 0.0, q2 = 0.0;
     for (int k = (int)threadIdx.x; k < np; k += 256) {
         q0 += part[3 * k];
         q1 += part[3 * k + 1];
-        q2 += part[3 * k + 2];
+        if (STEP == 2) q2 += part[3 * k + 2];
     }
-    const double u0 = block_sum256(q0), u1 = block_sum256(q1), u2 = block_sum256(q2);
-    if (threadIdx.x != 0) return;
+    const double u0 = block_sum256(q0), u1 = block_sum256(q1);
     if (STEP == 1) {
-        ksc[0] = u1;
-        ksc[1] = u1 > 0.0 ? u0 / u1 : 0.0;
+        o[0] = u1;
+        o[1] = u1 > 0.0 ? u0 / u1 : 0.0;
     } else {
+        const double u2 = block_sum256(q2);
         const double vv1 = ksc[0], a1 = ksc[1];
         const double g = vv1 > 0.0 ? u0 / vv1 : 0.0;
         const double den = u1 - g * u0;
         const double a2 = den > 0.0 ? u2 / den : 0.0;
-        ksc[2] = a1 - a2 * g;
-        ksc[3] = a2;
+        o[0] = a1 - a2 * g;
+        o[1] = a2;
     }
 }
 
-// b -= a1 v1 (b becomes r2) and the first sweep x = M b, one thread per node
-__global__ __launch_bounds__(256) void kstep_update(int32_t n, const double* __restrict__ v1,
-                                                    const double* __restrict__ ksc, const double* __restrict__ minv,
-                                                    double* __restrict__ b, double* __restrict__ x,
-                                                    const int32_t* __restrict__ fl) {
+// One workgroup: ksc[0] = (v1, v1), ksc[1] = a1 (STEP 1), ksc[2], ksc[3] =
+// the coefficients of c1 and c2 (STEP 2)
+template <int STEP>
+__global__ __launch_bounds__(256) void kstep_scalars(int np, const double* __restrict__ part, double* __restrict__ ksc,
+                                                     const int32_t* __restrict__ fl) {
     if (stopped(fl)) return;
+    double o[2];
+    kstep_coefficients<STEP>(np, part, ksc, o);
+    if (threadIdx.x != 0) return;
+    ksc[STEP == 1 ? 0 : 2] = o[0];
+    ksc[STEP == 1 ? 1 : 3] = o[1];
+}
+
+// b -= a1 v1 (b becomes r2) and the first sweep x = M b, one thread per
+// node.  np > 0: a1 from the product's partials, left in ksc for the second
+// step; np = 0: ksc[1].
+__global__ __launch_bounds__(256) void kstep_update(int32_t n, const double* __restrict__ v1, int np,
+                                                    const double* __restrict__ part, double* __restrict__ ksc,
+                                                    const double* __restrict__ minv, double* __restrict__ b,
+                                                    double* __restrict__ x, const int32_t* __restrict__ fl) {
+    if (stopped(fl)) return;
+    double a1;
+    if (np > 0) {
+        double o[2];
+        kstep_coefficients<1>(np, part, ksc, o);
+        a1 = o[1];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ksc[0] = o[0];
+            ksc[1] = o[1];
+        }
+    } else {
+        a1 = ksc[1];
+    }
     const int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (I >= n) return;
-    const double a1 = ksc[1];
     double r[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -807,19 +1126,89 @@ __global__ __launch_bounds__(256) void kstep_update(int32_t n, const double* __r
     for (int a = 0; a < 3; ++a) x[3 * I + a] = m[3 * a] * r[0] + m[3 * a + 1] * r[1] + m[3 * a + 2] * r[2];
 }
 
-// x_fine += P (e1 c1 + e2 c2) (masked), e1, e2 = ksc[2], ksc[3] of the coarse level
+// x_fine += P (e1 c1 + e2 c2) (masked); e1, e2 of the coarse level's second
+// step from its partials (np > 0) or from ksc[2], ksc[3]
 __global__ __launch_bounds__(256) void kprolong_kernel(int32_t n, const int32_t* __restrict__ agg,
                                                        const uint8_t* __restrict__ fmask, const double* __restrict__ c1,
-                                                       const double* __restrict__ c2, const double* __restrict__ ksc,
+                                                       const double* __restrict__ c2, int np,
+                                                       const double* __restrict__ part, const double* __restrict__ ksc,
                                                        double* __restrict__ x, const int32_t* __restrict__ fl) {
     if (stopped(fl)) return;
+    double e[2];
+    if (np > 0) {
+        kstep_coefficients<2>(np, part, ksc, e);
+    } else {
+        e[0] = ksc[2];
+        e[1] = ksc[3];
+    }
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double e1 = ksc[2], e2 = ksc[3];
     const int64_t C = agg[i];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
-        if (fmask[3 * i + a]) x[3 * i + a] += e1 * c1[3 * C + a] + e2 * c2[3 * C + a];
+        if (fmask[3 * i + a]) x[3 * i + a] += e[0] * c1[3 * C + a] + e[1] * c2[3 * C + a];
+}
+
+// Prolongation and second sweep of a small level in one kernel: with
+// x' = x + P y (KSTEP: P (e1 y + e2 y2), coefficients as in
+// kprolong_kernel), out = x' + M (b - A x'); rows as in post_kernel.
+template <bool KSTEP>
+__global__ __launch_bounds__(256) void post_prolong_kernel(
+    int32_t n, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ ncol, const float* __restrict__ val,
+    const double* __restrict__ x, const double* __restrict__ b, const double* __restrict__ minv,
+    const int32_t* __restrict__ aggm, const double* __restrict__ y, const double* __restrict__ y2, int np,
+    const double* __restrict__ part, const double* __restrict__ ksc, double* __restrict__ out,
+    const int32_t* __restrict__ fl) {
+    if (stopped(fl)) return;
+    double e[2] = {1.0, 0.0};
+    if (KSTEP) {
+        if (np > 0) {
+            kstep_coefficients<2>(np, part, ksc, e);
+        } else {
+            e[0] = ksc[2];
+            e[1] = ksc[3];
+        }
+    }
+    auto corrected = [&](int64_t J, double o[3]) {
+        const uint32_t am = (uint32_t)aggm[J];
+        const int64_t c = 3 * (int64_t)(am & 0x0fffffffu);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double p = KSTEP ? e[0] * y[c + a] + e[1] * y2[c + a] : y[c + a];
+            o[a] = x[3 * J + a] + (((am >> (28 + a)) & 1u) ? p : 0.0);
+        }
+    };
+    const int l = (int)(threadIdx.x & (kLanes - 1));
+    for (int64_t base = (int64_t)blockIdx.x * 8; base < n; base += (int64_t)gridDim.x * 8) {
+        const int64_t I = base + (threadIdx.x >> 5);
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        if (I < n) {
+            const int32_t bs = row_ptr[3 * I], len = row_ptr[3 * I + 1] - bs, deg = len / 3;
+            const int32_t* __restrict__ nc = ncol + bs / 9;
+            for (int32_t k = l; k < deg; k += kLanes) {
+                double q[3];
+                corrected(nc[k], q);
+                const float* __restrict__ v = val + bs + 3 * k;
+                s0 += (double)v[0] * q[0] + (double)v[1] * q[1] + (double)v[2] * q[2];
+                s1 += (double)v[len] * q[0] + (double)v[len + 1] * q[1] + (double)v[len + 2] * q[2];
+                s2 += (double)v[2 * len] * q[0] + (double)v[2 * len + 1] * q[1] + (double)v[2 * len + 2] * q[2];
+            }
+        }
+#pragma unroll
+        for (int m = 1; m < kLanes; m <<= 1) {
+            s0 += __shfl_xor(s0, m, kLanes);
+            s1 += __shfl_xor(s1, m, kLanes);
+            s2 += __shfl_xor(s2, m, kLanes);
+        }
+        if (I < n && l < 3) {
+            const double r0 = b[3 * I] - s0, r1 = b[3 * I + 1] - s1, r2 = b[3 * I + 2] - s2;
+            const double* m = minv + 9 * I;
+            double q[3];
+            corrected(I, q);
+            out[3 * I + l] = (l == 0 ? q[0] : (l == 1 ? q[1] : q[2])) + m[3 * l] * r0 + m[3 * l + 1] * r1 +
+                             m[3 * l + 2] * r2;
+        }
+    }
 }
 
 inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
@@ -1058,6 +1447,123 @@ bool build_hierarchy(std::vector<HostLevel>& H) {
     return true;
 }
 
+// First level of the single-workgroup tail (nl if no level is small enough)
+template <typename N>
+int tail_from(int nl, N&& nodes) {
+    for (int l = 1; l < nl; ++l)
+        if (nodes(l) <= kTailNodes) return l;
+    return nl;
+}
+
+// Packed form of the tail levels t, ..., nl - 1 on the host; false if they do
+// not fit tail_packed_kernel.
+struct HostTail {
+    std::vector<int32_t> psrc, plen;
+    std::vector<uint64_t> pc;
+    std::vector<int4> row;
+    std::vector<uint4> mem;
+};
+
+bool plan_tail(const std::vector<HostLevel>& H, int t, bool dense, std::vector<HostTail>& P, size_t* lds) {
+    const int nl = (int)H.size();
+    if (t >= nl) return false;
+    P.assign(nl, HostTail());
+    size_t nodes = 0, seg_max = 0, low = 0;
+    for (int l = t; l < nl; ++l) {
+        const HostLevel& h = H[l];
+        HostTail& o = P[l];
+        nodes += h.n;
+        const bool op = !(dense && l == nl - 1);
+        o.row.resize(h.n);
+        std::vector<int32_t> first(h.n);
+        int32_t ns = 0;
+        for (int32_t I = 0; I < h.n; ++I) {
+            const int32_t deg = (int32_t)(h.bptr[I + 1] - h.bptr[I]), k = op ? (deg + kSeg - 1) / kSeg : 0;
+            int32_t w = 0;
+            for (int a = 0; a < 3; ++a) w |= h.mask[3 * (size_t)I + a] ? 1 << a : 0;
+            if (l > t) w |= (h.mptr[I + 1] - h.mptr[I]) << 8;
+            o.row[I] = make_int4(ns, k, l + 1 < nl ? H[l + 1].agg[I] : 0, w);
+            first[I] = ns;
+            ns += k;
+        }
+        if (l > t) {
+            o.mem.resize(h.n);
+            for (int32_t I = 0; I < h.n; ++I) {
+                uint32_t w[4] = {0, 0, 0, 0};
+                for (int32_t k = h.mptr[I]; k < h.mptr[I + 1]; ++k) {
+                    const int q = k - h.mptr[I];
+                    w[q >> 1] |= (uint32_t)h.mem[k] << (16 * (q & 1));
+                }
+                o.mem[I] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        }
+        o.psrc.assign((size_t)kSeg * ns, -1);
+        o.plen.assign(ns, 0);
+        o.pc.assign(ns, 0);
+        for (int32_t I = 0; op && I < h.n; ++I) {
+            const int32_t deg = (int32_t)(h.bptr[I + 1] - h.bptr[I]);
+            for (int32_t k = 0; k < deg; ++k) {
+                const int32_t g = first[I] + k / kSeg, j = k % kSeg;
+                o.psrc[(size_t)j * ns + g] = (int32_t)(9 * h.bptr[I] + 3 * k);
+                o.plen[g] = 3 * deg;
+                o.pc[g] |= (uint64_t)h.ncol[h.bptr[I] + k] << (16 * j);
+            }
+        }
+        if (l == t && ns > kTailSeg0) return false;
+        seg_max = std::max(seg_max, (size_t)ns);
+        if (l > t) low += (size_t)ns * (36 * kSeg + 8);
+    }
+    // vectors, residual, segment sums, the smaller levels' values; the
+    // smoother blocks and the coarsest inverse too where they fit
+    *lds = 24 * (nodes + H[t].n + seg_max) + low;
+    const size_t inv = dense ? sizeof(double) * 9 * (size_t)H[nl - 1].n * H[nl - 1].n : 0;
+    if (*lds + 72 * nodes <= kTailLds) *lds += 72 * nodes;
+    if (*lds + inv <= kTailLds) *lds += inv;
+    return nodes <= kTailThreads && *lds <= kTailLds;
+}
+
+// Arguments of tail_packed_kernel for levels t, ...; the LDS layout follows
+// plan_tail.
+void tail_args(const fem_amg* h, int t, TailPacked& A) {
+    std::memset(&A, 0, sizeof A);
+    A.nlv = h->nl - t;
+    A.dense = h->dense ? 1 : 0;
+    A.nd = h->nd;
+    A.cinv = h->cinv;
+    A.b = h->L[t].b;
+    A.x = h->L[t].x;
+    A.y = (A.nlv == 1 && h->dense) ? h->L[t].x : h->L[t].y;
+    int32_t own = 0, off = 0, seg = 0;
+    for (int l = 0; l < A.nlv; ++l) {
+        const Level& S = h->L[t + l];
+        TailPackedLevel& T = A.L[l];
+        T.n = S.n;
+        T.ns = S.ns;
+        T.own = own;
+        T.x = off;
+        T.pv = S.pv;
+        T.pc = S.pc;
+        T.row = S.prow;
+        T.mem = S.pmem;
+        T.minv = S.minv;
+        own += S.n;
+        off += 3 * S.n;
+        seg = std::max(seg, S.ns);
+    }
+    A.oR = off;
+    A.oC = A.oR + 3 * h->L[t].n;
+    off = A.oC + 3 * seg;
+    for (int l = 1; l < A.nlv; ++l) {
+        A.L[l].v = off;
+        off += (36 * kSeg + 8) / 8 * A.L[l].ns;
+    }
+    const bool sm = (size_t)8 * (off + 9 * (size_t)own) <= kTailLds;
+    A.oM = sm ? off : -1;
+    if (sm) off += 9 * own;
+    const bool inv = h->dense && (size_t)8 * (off + (size_t)h->nd * h->nd) <= kTailLds;
+    A.oI = inv ? off : -1;
+}
+
 // Damped block-Jacobi blocks of level l (values V): the inverses of the
 // diagonal blocks, then omega_l from the power iteration (levels that are
 // inverted exactly keep omega = 1: their smoother is not used).
@@ -1096,6 +1602,13 @@ hipError_t update_typed(fem_amg* h, const RV* K, hipStream_t s) {
                                c.glen, c.gmask, c.gdst, c.gdlen, c.gfix, (const float*)f.vals, c.vals);
         smoother_setup(h, l, (const float*)c.vals, s);
     }
+    if (h->packed)
+        for (int l = 1; l < h->nl; ++l) {
+            const Level& c = h->L[l];
+            if (c.ns > 0)
+                hipLaunchKernelGGL(tail_pack_kernel, dim3(blocks_for((int64_t)kSeg * c.ns)), dim3(256), 0, s, c.ns,
+                                   c.psrc, c.plen, (const float*)c.vals, c.pv);
+        }
     if (h->dense) {
         const Level& c = h->L[h->nl - 1];
         if (h->nl == 1)
@@ -1151,11 +1664,8 @@ bool amg_matches(const fem_amg* h, const fem_csr* csr) {
 
 namespace {
 
-// first level of the single-workgroup tail (nl if no level is small enough)
 int tail_start(const fem_amg* h) {
-    for (int l = 1; l < h->nl; ++l)
-        if (h->L[l].n <= kTailNodes) return l;
-    return h->nl;
+    return tail_from(h->nl, [&](int l) { return h->L[l].n; });
 }
 
 // level c takes the two K-cycle steps: a level above the tail, not the
@@ -1172,6 +1682,10 @@ const double* cycle_from(fem_amg* h, int l, const double* bl, double* out, int t
     Level* L = h->L;
     const int nl = h->nl;
     if (l >= t) {  // levels t, ..., nl - 1 in one workgroup
+        if (h->packed) {
+            hipLaunchKernelGGL(tail_packed_kernel, dim3(1), dim3(kTailThreads), h->tail_lds, s, h->tail, fl);
+            return (t == nl - 1 && h->dense) ? L[t].x : L[t].y;
+        }
         TailArgs A;
         A.nlv = nl - t;
         A.dense = h->dense ? 1 : 0;
@@ -1215,24 +1729,44 @@ const double* cycle_from(fem_amg* h, int l, const double* bl, double* out, int t
         hipLaunchKernelGGL(resid_restrict_kernel<float>, dim3(C.n), dim3(256), 0, s, C.mptr, C.mem, L[0].mask,
                            L[0].row_ptr, L[0].ncol, static_cast<const float*>(h->K), L[0].x, bl, C.minv, C.b, C.x,
                            fl);
+    const unsigned nf = blocks_for(L[l].n);
+    const unsigned nbp = std::min<unsigned>(kPostGrid, blocks_for((int64_t)L[l].n * kLanes));
+    const bool fuse = l > 0 && C.aggm;
     if (krylov_level(h, c, t)) {
         const unsigned ng = std::min<unsigned>(kPostGrid, blocks_for((int64_t)C.n * kLanes));
+        const unsigned nu = blocks_for(C.n);
+        const bool own1 = (int64_t)nu * ng <= kFusePartials;
+        const bool own2 = (int64_t)(fuse ? nbp : nf) * ng <= kFusePartials;
+        const int np1 = own1 ? (int)ng : 0, np2 = own2 ? (int)ng : 0;
+        const double* part = C.kpart;
         cycle_from(h, c, C.b, C.kc1, t, fl, s);
         hipLaunchKernelGGL(kstep_product<1>, dim3(ng), dim3(256), 0, s, C.n, C.row_ptr, C.ncol,
                            (const float*)C.vals, (const double*)C.kc1, (const double*)C.b, C.kv1, C.kpart, fl);
-        hipLaunchKernelGGL(kstep_scalars<1>, dim3(1), dim3(256), 0, s, (int)ng, (const double*)C.kpart, C.ksc, fl);
-        hipLaunchKernelGGL(kstep_update, dim3(blocks_for(C.n)), dim3(256), 0, s, C.n, (const double*)C.kv1,
-                           (const double*)C.ksc, (const double*)C.minv, C.b, C.x, fl);
+        if (!own1) hipLaunchKernelGGL(kstep_scalars<1>, dim3(1), dim3(256), 0, s, (int)ng, part, C.ksc, fl);
+        hipLaunchKernelGGL(kstep_update, dim3(nu), dim3(256), 0, s, C.n, (const double*)C.kv1, np1, part, C.ksc,
+                           (const double*)C.minv, C.b, C.x, fl);
         cycle_from(h, c, C.b, C.y, t, fl, s);
         hipLaunchKernelGGL(kstep_product<2>, dim3(ng), dim3(256), 0, s, C.n, C.row_ptr, C.ncol,
                            (const float*)C.vals, (const double*)C.y, (const double*)C.b, C.kv1, C.kpart, fl);
-        hipLaunchKernelGGL(kstep_scalars<2>, dim3(1), dim3(256), 0, s, (int)ng, (const double*)C.kpart, C.ksc, fl);
-        hipLaunchKernelGGL(kprolong_kernel, dim3(blocks_for(L[l].n)), dim3(256), 0, s, L[l].n, C.agg, L[l].mask,
-                           (const double*)C.kc1, (const double*)C.y, (const double*)C.ksc, L[l].x, fl);
+        if (!own2) hipLaunchKernelGGL(kstep_scalars<2>, dim3(1), dim3(256), 0, s, (int)ng, part, C.ksc, fl);
+        if (fuse) {
+            hipLaunchKernelGGL(post_prolong_kernel<true>, dim3(nbp), dim3(256), 0, s, L[l].n, L[l].row_ptr, L[l].ncol,
+                               (const float*)L[l].vals, (const double*)L[l].x, bl, (const double*)L[l].minv, C.aggm,
+                               (const double*)C.kc1, (const double*)C.y, np2, part, (const double*)C.ksc, out, fl);
+            return out;
+        }
+        hipLaunchKernelGGL(kprolong_kernel, dim3(nf), dim3(256), 0, s, L[l].n, C.agg, L[l].mask,
+                           (const double*)C.kc1, (const double*)C.y, np2, part, (const double*)C.ksc, L[l].x, fl);
     } else {
         const double* yc = cycle_from(h, c, C.b, C.y, t, fl, s);
-        hipLaunchKernelGGL(prolong_kernel, dim3(blocks_for(L[l].n)), dim3(256), 0, s, L[l].n, C.agg, L[l].mask, yc,
-                           L[l].x, fl);
+        if (fuse) {
+            hipLaunchKernelGGL(post_prolong_kernel<false>, dim3(nbp), dim3(256), 0, s, L[l].n, L[l].row_ptr,
+                               L[l].ncol, (const float*)L[l].vals, (const double*)L[l].x, bl,
+                               (const double*)L[l].minv, C.aggm, yc, (const double*)nullptr, 0,
+                               (const double*)nullptr, (const double*)nullptr, out, fl);
+            return out;
+        }
+        hipLaunchKernelGGL(prolong_kernel, dim3(nf), dim3(256), 0, s, L[l].n, C.agg, L[l].mask, yc, L[l].x, fl);
     }
     level_post(h, l, L[l].x, bl, out, fl, s);
     return out;
@@ -1335,6 +1869,12 @@ extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precis
     const int nl = (int)H.size();
     const bool dense = H.back().n <= FEM_AMG_DENSE_NODES;
 
+    const int tail = tail_from(nl, [&](int l) { return H[l].n; });
+    std::vector<HostTail> packs;
+    size_t tail_lds = 0;
+    const bool packed = plan_tail(H, tail, dense, packs, &tail_lds);
+    // level l takes its prolongation inside the second sweep (aggm of level l + 1)
+    auto fused = [&](int l) { return l > 0 && l < tail && l + 1 < nl && H[l].n <= kFuseNodes; };
     // one device allocation
     auto sizes = [&](WsCounter& c) {
         for (int l = 0; l < nl; ++l) {
@@ -1365,12 +1905,23 @@ extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precis
                 c.take<double>(3 * n);
                 c.take<double>(3 * kPostGrid);
                 c.take<double>(4);
+                if (fused(l - 1)) c.take<int32_t>(nf);
+                if (packed && l >= tail) {
+                    const size_t ns = packs[l].pc.size();
+                    c.take<float>(9 * kSeg * ns);
+                    c.take<uint64_t>(ns);
+                    c.take<int32_t>(kSeg * ns);
+                    c.take<int32_t>(ns);
+                    c.take<int4>(n);
+                    c.take<uint4>(n);
+                }
             }
         }
         if (dense) c.take<double>((size_t)9 * H.back().n * H.back().n);
         c.take<double>(FEM_AMG_MAX_LEVELS);
         c.take<double>(2 * FEM_AMG_MAX_LEVELS);
         c.take<double>(std::max<int64_t>(blocks_for(3 * (int64_t)H[0].n), kPowerGrid) + 1);
+        if (packed) c.take<TailPacked>(1);
     };
     WsCounter cnt;
     sizes(cnt);
@@ -1388,6 +1939,8 @@ extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precis
     h->nl = nl;
     h->dense = dense;
     h->nd = 3 * H.back().n;
+    h->packed = packed;
+    h->tail_lds = tail_lds;
     WsCarver cv(h->mem, bytes);
     double ones[FEM_AMG_MAX_LEVELS];  // initial damping (kept alive until the synchronisation below)
     for (double& o : ones) o = 1.0;
@@ -1395,7 +1948,7 @@ extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precis
     auto up = [&](void* dst, const void* src, size_t nbytes) {
         if (e == hipSuccess && nbytes) e = hipMemcpyAsync(dst, src, nbytes, hipMemcpyHostToDevice, s);
     };
-    std::vector<std::vector<int32_t>> rowps(nl);
+    std::vector<std::vector<int32_t>> rowps(nl), aggms(nl);
     for (int l = 0; l < nl; ++l) {
         const HostLevel& hl = H[l];
         Level& L = h->L[l];
@@ -1443,6 +1996,34 @@ extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precis
             L.kv1 = cv.take<double>(3 * n);
             L.kpart = cv.take<double>(3 * kPostGrid);
             L.ksc = cv.take<double>(4);
+            if (fused(l - 1)) {
+                L.aggm = cv.take<int32_t>(nf);
+                std::vector<int32_t>& am = aggms[l];
+                am.resize(nf);
+                const HostLevel& f = H[l - 1];
+                for (size_t i = 0; i < nf; ++i) {
+                    uint32_t w = (uint32_t)hl.agg[i];
+                    for (int a = 0; a < 3; ++a) w |= f.mask[3 * i + a] ? 1u << (28 + a) : 0u;
+                    am[i] = (int32_t)w;
+                }
+                up(L.aggm, am.data(), nf * 4);
+            }
+            if (packed && l >= tail) {
+                const HostTail& o = packs[l];
+                const size_t ns = o.pc.size();
+                L.ns = (int32_t)ns;
+                L.pv = cv.take<float>(9 * kSeg * ns);
+                L.pc = cv.take<uint64_t>(ns);
+                L.psrc = cv.take<int32_t>(kSeg * ns);
+                L.plen = cv.take<int32_t>(ns);
+                L.prow = cv.take<int4>(n);
+                L.pmem = cv.take<uint4>(n);
+                up(L.pc, o.pc.data(), ns * 8);
+                up(L.psrc, o.psrc.data(), kSeg * ns * 4);
+                up(L.plen, o.plen.data(), ns * 4);
+                up(L.prow, o.row.data(), n * sizeof(int4));
+                if (l > tail) up(L.pmem, o.mem.data(), n * sizeof(uint4));
+            }
             up(L.agg, hl.agg.data(), nf * 4);
             up(L.mptr, hl.mptr.data(), (n + 1) * 4);
             up(L.mem, hl.mem.data(), nf * 4);
@@ -1461,7 +2042,16 @@ extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precis
     h->npart = (int)std::max<int64_t>(blocks_for(3 * (int64_t)n0), kPowerGrid) + 1;
     h->part = cv.take<double>(h->npart);
     up(h->om, ones, sizeof ones);
+    TailPacked targs;
+    if (packed) {
+        h->tail = cv.take<TailPacked>(1);
+        tail_args(h, tail, targs);
+        up(h->tail, &targs, sizeof targs);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);  // host vectors are freed on return
+    if (e == hipSuccess && packed)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(tail_packed_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTailLds);
     if (e != hipSuccess || !cv.ok()) {
         (void)hipFree(h->mem);
         delete h;
