@@ -29,6 +29,7 @@
 #include <new>
 #include <vector>
 
+#include "block_rows.h"
 #include "fem_internal.h"
 
 namespace {
@@ -36,7 +37,7 @@ namespace {
 constexpr int kLanes = 32;                       // lanes per node of the block products
 constexpr int kDenseMax = 3 * FEM_AMG_DENSE_NODES;  // dofs of a dense coarsest level
 constexpr double kStall = 0.85;                  // stop when a level keeps more nodes than this
-constexpr int kPostGrid = 2048;                  // workgroup cap of the persistent level products
+constexpr int kPostGrid = 2048;                  // workgroup cap of the products that leave partial sums
 // The prolongation is folded into the post-smoothing product on levels of at
 // most this many nodes: a launch costs 4.8 us there (its few dependent loads,
 // not work) and the folded gather about 1 us.  On the finest level of 10^6
@@ -359,44 +360,99 @@ __global__ __launch_bounds__(256) void smooth0_kernel(int32_t n, const double* _
     for (int a = 0; a < 3; ++a) x[3 * I + a] = m[3 * a] * b0 + m[3 * a + 1] * b1 + m[3 * a + 2] * b2;
 }
 
-// Second sweep: out = x + M (b - A x); 32 lanes per node over a fixed grid
-// of at most kPostGrid workgroups (8 nodes per workgroup and round),
-// butterfly over the lanes in a fixed order
+// Second sweep: out = x + M (b - A x); 242 us on the finest level of the
+// 100^3 cube (1.34 GB; 332 us with 32 lanes per node straight from memory)
+struct PostEpilogue {
+    const double *x, *b, *minv;
+    double* out;
+    struct Data {
+        double b[3], m[3], x;
+    };
+    __device__ __forceinline__ Data load(int64_t I, int l) const {
+        Data d;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            d.b[a] = b[3 * I + a];
+            d.m[a] = minv[9 * I + 3 * l + a];
+        }
+        d.x = x[3 * I + l];
+        return d;
+    }
+    __device__ __forceinline__ void finish(int64_t I, int l, const Data& d, const double s[3]) const {
+        if (l < 3) {
+            const double r0 = d.b[0] - s[0], r1 = d.b[1] - s[1], r2 = d.b[2] - s[2];
+            out[3 * I + l] = d.x + d.m[0] * r0 + d.m[1] * r1 + d.m[2] * r2;
+        }
+    }
+};
 
-template <typename RV>
-__global__ __launch_bounds__(256) void post_kernel(int32_t n, const int32_t* __restrict__ row_ptr,
+template <typename RV, bool STAGED>
+__global__ __launch_bounds__(256, 4) void post_kernel(int32_t n, const int32_t* __restrict__ row_ptr,
                                                    const int32_t* __restrict__ ncol, const RV* __restrict__ val,
                                                    const double* __restrict__ x, const double* __restrict__ b,
                                                    const double* __restrict__ minv, double* __restrict__ out,
                                                    const int32_t* __restrict__ fl) {
     if (stopped(fl)) return;
-    const int l = (int)(threadIdx.x & (kLanes - 1));
-    for (int64_t base = (int64_t)blockIdx.x * 8; base < n; base += (int64_t)gridDim.x * 8) {
-        const int64_t I = base + (threadIdx.x >> 5);
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        if (I < n) {
-            const int32_t bs = row_ptr[3 * I], len = row_ptr[3 * I + 1] - bs, deg = len / 3;
-            const int32_t* __restrict__ nc = ncol + bs / 9;
-            for (int32_t k = l; k < deg; k += kLanes) {
-                const int64_t J = nc[k];
-                const double x0 = x[3 * J], x1 = x[3 * J + 1], x2 = x[3 * J + 2];
-                const RV* __restrict__ v = val + bs + 3 * k;
-                s0 += (double)v[0] * x0 + (double)v[1] * x1 + (double)v[2] * x2;
-                s1 += (double)v[len] * x0 + (double)v[len + 1] * x1 + (double)v[len + 2] * x2;
-                s2 += (double)v[2 * len] * x0 + (double)v[2 * len + 1] * x1 + (double)v[2 * len + 2] * x2;
-            }
-        }
+    PostEpilogue e{x, b, minv, out};
+    block_rows<RV, STAGED>(n, row_ptr, ncol, val, x, e);
+}
+
+// Residual on the free dofs, r = mask (b - A x), of a large level: the rows
+// in their order, the restriction in a kernel of its own.  On the finest
+// level of the 100^3 cube a workgroup per aggregate, whose eight rows lie
+// apart, took 303 us for both; this takes 208 and 15.
+struct ResidEpilogue {
+    const double* b;
+    const uint8_t* mask;
+    double* r;
+    struct Data {
+        double b;
+        uint8_t m;
+    };
+    __device__ __forceinline__ Data load(int64_t I, int l) const { return {b[3 * I + l], mask[3 * I + l]}; }
+    __device__ __forceinline__ void finish(int64_t I, int l, const Data& d, const double s[3]) const {
+        if (l < 3) r[3 * I + l] = d.m ? d.b - (l == 0 ? s[0] : (l == 1 ? s[1] : s[2])) : 0.0;
+    }
+};
+
+template <typename RV, bool STAGED>
+__global__ __launch_bounds__(256, 4) void resid_kernel(int32_t n, const int32_t* __restrict__ row_ptr,
+                                                    const int32_t* __restrict__ ncol, const RV* __restrict__ val,
+                                                    const double* __restrict__ x, const double* __restrict__ b,
+                                                    const uint8_t* __restrict__ mask, double* __restrict__ r,
+                                                    const int32_t* __restrict__ fl) {
+    if (stopped(fl)) return;
+    ResidEpilogue e{b, mask, r};
+    block_rows<RV, STAGED>(n, row_ptr, ncol, val, x, e);
+}
+
+// cb = P^T r (r zero on constrained dofs), cx = M_c cb; one thread per coarse node
+__global__ __launch_bounds__(256) void restrict_kernel(int32_t nc, const int32_t* __restrict__ mptr,
+                                                       const int32_t* __restrict__ mem, const double* __restrict__ r,
+                                                       const double* __restrict__ cminv, double* __restrict__ cb,
+                                                       double* __restrict__ cx, const int32_t* __restrict__ fl) {
+    if (stopped(fl)) return;
+    const int64_t C = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (C >= nc) return;
+    const int32_t m0 = mptr[C], cnt = mptr[C + 1] - m0;
+    double v[8][3];
 #pragma unroll
-        for (int m = 1; m < kLanes; m <<= 1) {
-            s0 += __shfl_xor(s0, m, kLanes);
-            s1 += __shfl_xor(s1, m, kLanes);
-            s2 += __shfl_xor(s2, m, kLanes);
-        }
-        if (I < n && l < 3) {
-            const double r0 = b[3 * I] - s0, r1 = b[3 * I + 1] - s1, r2 = b[3 * I + 2] - s2;
-            const double* m = minv + 9 * I;
-            out[3 * I + l] = x[3 * I + l] + m[3 * l] * r0 + m[3 * l + 1] * r1 + m[3 * l + 2] * r2;
-        }
+    for (int k = 0; k < 8; ++k) {  // at most eight members; all requested before the first is added
+        const int64_t i = mem[m0 + min(k, cnt - 1)];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) v[k][a] = r[3 * i + a];
+    }
+    double t[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (k < cnt)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) t[a] += v[k][a];
+    const double* m = cminv + 9 * C;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        cb[3 * C + a] = t[a];
+        cx[3 * C + a] = m[3 * a] * t[0] + m[3 * a + 1] * t[1] + m[3 * a + 2] * t[2];
     }
 }
 
@@ -886,18 +942,29 @@ constexpr int kPowerSteps = 10;
 constexpr double kOmegaNum = 4.0 / 3.0;
 constexpr double kOmegaFallback = 0.5;  // for a non-positive or non-finite estimate
 
-// Fixed-order sum of one value per thread of a 256-thread block.
-__device__ inline double block_sum256(double v) {
-    __shared__ double sh[256];
+// Fixed-order sums of N values per thread of a 256-thread block, in every
+// thread: the two halves of each wave, then the eight sums.
+template <int N>
+__device__ __forceinline__ void block_sums(double v[N]) {
+    __shared__ double sh[8][N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = sum32(v[k]);
     __syncthreads();
-    sh[threadIdx.x] = v;
+    if ((threadIdx.x & 31) == 0)
+#pragma unroll
+        for (int k = 0; k < N; ++k) sh[threadIdx.x >> 5][k] = v[k];
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double a = (sh[0][k] + sh[1][k]) + (sh[2][k] + sh[3][k]);
+        v[k] = a + ((sh[4][k] + sh[5][k]) + (sh[6][k] + sh[7][k]));
     }
-    return sh[0];
 }
+__device__ __forceinline__ double block_sum256(double v) {
+    block_sums<1>(&v);
+    return v;
+}
+__device__ __forceinline__ void block_sum3(double v[3]) { block_sums<3>(v); }
 
 // v[i] = value in [-1, 1) from an integer hash of i (a SplitMix64-style
 // finaliser) on free dofs, 0 on constrained ones; part = block sums of v.v
@@ -924,44 +991,38 @@ __global__ __launch_bounds__(256) void power_init(int64_t n3, const uint8_t* __r
 // of w.w per workgroup
 constexpr int kPowerGrid = 2048;
 
-template <typename RV>
-__global__ __launch_bounds__(256) void power_apply(int32_t n, const int32_t* __restrict__ row_ptr,
-                                                   const int32_t* __restrict__ ncol, const RV* __restrict__ val,
-                                                   const double* __restrict__ minv, const double* __restrict__ v,
-                                                   const double* __restrict__ sc, double* __restrict__ w,
-                                                   double* __restrict__ part) {
-    const int l = (int)(threadIdx.x & (kLanes - 1));
-    const double scale = sc[1];
-    double ww = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * 8; base < n; base += (int64_t)gridDim.x * 8) {
-        const int64_t I = base + (threadIdx.x >> 5);
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        if (I < n) {
-            const int32_t bs = row_ptr[3 * I], len = row_ptr[3 * I + 1] - bs, deg = len / 3;
-            const int32_t* __restrict__ nc = ncol + bs / 9;
-            for (int32_t k = l; k < deg; k += kLanes) {
-                const int64_t J = nc[k];
-                const double x0 = v[3 * J], x1 = v[3 * J + 1], x2 = v[3 * J + 2];
-                const RV* __restrict__ q = val + bs + 3 * k;
-                s0 += (double)q[0] * x0 + (double)q[1] * x1 + (double)q[2] * x2;
-                s1 += (double)q[len] * x0 + (double)q[len + 1] * x1 + (double)q[len + 2] * x2;
-                s2 += (double)q[2 * len] * x0 + (double)q[2 * len + 1] * x1 + (double)q[2 * len + 2] * x2;
-            }
-        }
+struct PowerEpilogue {
+    const double* minv;
+    double scale;
+    double* w;
+    double ww;
+    struct Data {
+        double m[3];
+    };
+    __device__ __forceinline__ Data load(int64_t I, int l) const {
+        Data d;
 #pragma unroll
-        for (int m = 1; m < kLanes; m <<= 1) {
-            s0 += __shfl_xor(s0, m, kLanes);
-            s1 += __shfl_xor(s1, m, kLanes);
-            s2 += __shfl_xor(s2, m, kLanes);
-        }
-        if (I < n && l < 3) {
-            const double* m = minv + 9 * I;
-            const double wl = scale * (m[3 * l] * s0 + m[3 * l + 1] * s1 + m[3 * l + 2] * s2);
+        for (int a = 0; a < 3; ++a) d.m[a] = minv[9 * I + 3 * l + a];
+        return d;
+    }
+    __device__ __forceinline__ void finish(int64_t I, int l, const Data& d, const double s[3]) {
+        if (l < 3) {
+            const double wl = scale * (d.m[0] * s[0] + d.m[1] * s[1] + d.m[2] * s[2]);
             w[3 * I + l] = wl;
             ww += wl * wl;
         }
     }
-    const double t = block_sum256(ww);
+};
+
+template <typename RV, bool STAGED>
+__global__ __launch_bounds__(256, 4) void power_apply(int32_t n, const int32_t* __restrict__ row_ptr,
+                                                   const int32_t* __restrict__ ncol, const RV* __restrict__ val,
+                                                   const double* __restrict__ minv, const double* __restrict__ v,
+                                                   const double* __restrict__ sc, double* __restrict__ w,
+                                                   double* __restrict__ part) {
+    PowerEpilogue e{minv, sc[1], w, 0.0};
+    block_rows<RV, STAGED>(n, row_ptr, ncol, val, v, e);
+    const double t = block_sum256(e.ww);
     if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
@@ -1000,56 +1061,49 @@ __global__ __launch_bounds__(256) void power_finish(int32_t n, const double* __r
 
 // STEP 1: v1 = A c (stored), part = workgroup sums of (v1, b), (v1, v1).
 // STEP 2: v2 = A c (not stored), part = workgroup sums of (v2, v1),
-// (v2, v2), (v2, b).  Rows by 32 lanes as in post_kernel.
+// (v2, v2), (v2, b).
 template <int STEP>
-__global__ __launch_bounds__(256) void kstep_product(int32_t n, const int32_t* __restrict__ row_ptr,
+struct KstepEpilogue {
+    const double* b;
+    double* v1;
+    double d0, d1, d2;
+    struct Data {
+        double b, v;
+    };
+    __device__ __forceinline__ Data load(int64_t I, int l) const {
+        return {b[3 * I + l], STEP == 2 ? v1[3 * I + l] : 0.0};
+    }
+    __device__ __forceinline__ void finish(int64_t I, int l, const Data& d, const double s[3]) {
+        if (l < 3) {
+            const double va = l == 0 ? s[0] : (l == 1 ? s[1] : s[2]);
+            if (STEP == 1) {
+                v1[3 * I + l] = va;
+                d0 += va * d.b;
+                d1 += va * va;
+            } else {
+                d0 += va * d.v;
+                d1 += va * va;
+                d2 += va * d.b;
+            }
+        }
+    }
+};
+
+template <int STEP, bool STAGED>
+__global__ __launch_bounds__(256, 4) void kstep_product(int32_t n, const int32_t* __restrict__ row_ptr,
                                                      const int32_t* __restrict__ ncol, const float* __restrict__ val,
                                                      const double* __restrict__ c, const double* __restrict__ b,
                                                      double* __restrict__ v1, double* __restrict__ part,
                                                      const int32_t* __restrict__ fl) {
     if (stopped(fl)) return;
-    const int l = (int)(threadIdx.x & (kLanes - 1));
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * 8; base < n; base += (int64_t)gridDim.x * 8) {
-        const int64_t I = base + (threadIdx.x >> 5);
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        if (I < n) {
-            const int32_t bs = row_ptr[3 * I], len = row_ptr[3 * I + 1] - bs, deg = len / 3;
-            const int32_t* __restrict__ nc = ncol + bs / 9;
-            for (int32_t k = l; k < deg; k += kLanes) {
-                const int64_t J = nc[k];
-                const double x0 = c[3 * J], x1 = c[3 * J + 1], x2 = c[3 * J + 2];
-                const float* __restrict__ v = val + bs + 3 * k;
-                s0 += (double)v[0] * x0 + (double)v[1] * x1 + (double)v[2] * x2;
-                s1 += (double)v[len] * x0 + (double)v[len + 1] * x1 + (double)v[len + 2] * x2;
-                s2 += (double)v[2 * len] * x0 + (double)v[2 * len + 1] * x1 + (double)v[2 * len + 2] * x2;
-            }
-        }
-#pragma unroll
-        for (int m = 1; m < kLanes; m <<= 1) {
-            s0 += __shfl_xor(s0, m, kLanes);
-            s1 += __shfl_xor(s1, m, kLanes);
-            s2 += __shfl_xor(s2, m, kLanes);
-        }
-        if (I < n && l < 3) {
-            const int64_t k = 3 * I + l;
-            const double va = l == 0 ? s0 : (l == 1 ? s1 : s2);
-            if (STEP == 1) {
-                v1[k] = va;
-                d0 += va * b[k];
-                d1 += va * va;
-            } else {
-                d0 += va * v1[k];
-                d1 += va * va;
-                d2 += va * b[k];
-            }
-        }
-    }
-    const double t0 = block_sum256(d0), t1 = block_sum256(d1), t2 = STEP == 2 ? block_sum256(d2) : 0.0;
+    KstepEpilogue<STEP> e{b, v1, 0.0, 0.0, 0.0};
+    block_rows<float, STAGED>(n, row_ptr, ncol, val, c, e);
+    double t[3] = {e.d0, e.d1, e.d2};
+    block_sum3(t);
     if (threadIdx.x == 0) {
-        part[3 * blockIdx.x] = t0;
-        part[3 * blockIdx.x + 1] = t1;
-        part[3 * blockIdx.x + 2] = t2;
+        part[3 * blockIdx.x] = t[0];
+        part[3 * blockIdx.x + 1] = t[1];
+        part[3 * blockIdx.x + 2] = t[2];
     }
 }
 
@@ -1065,12 +1119,14 @@ __device__ inline void kstep_coefficients(int np, const double* __restrict__ par
         q1 += part[3 * k + 1];
         if (STEP == 2) q2 += part[3 * k + 2];
     }
-    const double u0 = block_sum256(q0), u1 = block_sum256(q1);
+    double t[3] = {q0, q1, q2};
+    block_sum3(t);
+    const double u0 = t[0], u1 = t[1];
     if (STEP == 1) {
         o[0] = u1;
         o[1] = u1 > 0.0 ? u0 / u1 : 0.0;
     } else {
-        const double u2 = block_sum256(q2);
+        const double u2 = t[2];
         const double vv1 = ksc[0], a1 = ksc[1];
         const double g = vv1 > 0.0 ? u0 / vv1 : 0.0;
         const double den = u1 - g * u0;
@@ -1212,6 +1268,20 @@ __global__ __launch_bounds__(256) void post_prolong_kernel(
 }
 
 inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
+
+// Grid of a product over n rows of RV values.
+template <typename RV>
+unsigned product_grid(int32_t n, unsigned cap) {
+    return fem::row_blocks(n, n > fem::kStagedMin, fem::kStagedNodes<RV>, cap);
+}
+#define FEM_PRODUCT(KERNEL, RV, grid, n, ...)                                                                     \
+    do {                                                                                                          \
+        if ((n) > fem::kStagedMin)                                                                                \
+            hipLaunchKernelGGL((KERNEL<RV, true>), dim3(grid), dim3(256), 0, s, n, __VA_ARGS__);                  \
+        else                                                                                                      \
+            hipLaunchKernelGGL((KERNEL<RV, false>), dim3(grid), dim3(256), 0, s, n, __VA_ARGS__);                 \
+    } while (0)
+constexpr unsigned kNoCap = 1u << 30;
 
 // ---- host-side symbolic set-up
 
@@ -1577,12 +1647,11 @@ void smoother_setup(fem_amg* h, int l, const V* vals, hipStream_t s) {
     const unsigned nbi = blocks_for(3 * (int64_t)L.n);
     hipLaunchKernelGGL(power_init, dim3(nbi), dim3(256), 0, s, 3 * (int64_t)L.n, L.mask, L.r, h->part);
     hipLaunchKernelGGL(power_norm, dim3(1), dim3(256), 0, s, h->part, (int)nbi, sc);
-    const unsigned npg = std::min<unsigned>(kPowerGrid, blocks_for((int64_t)L.n * kLanes));
+    const unsigned npg = product_grid<V>(L.n, kPowerGrid);
     for (int k = 0; k < kPowerSteps; ++k) {
         const double* v = (k & 1) ? L.y : L.r;
         double* w = (k & 1) ? L.r : L.y;
-        hipLaunchKernelGGL(power_apply<V>, dim3(npg), dim3(256), 0, s, L.n, L.row_ptr, L.ncol, vals, L.minv, v, sc, w,
-                           h->part);
+        FEM_PRODUCT(power_apply, V, npg, L.n, L.row_ptr, L.ncol, vals, L.minv, v, sc, w, h->part);
         hipLaunchKernelGGL(power_norm, dim3(1), dim3(256), 0, s, h->part, (int)npg, sc);
     }
     hipLaunchKernelGGL(power_finish, dim3(blocks_for(9 * (int64_t)L.n)), dim3(256), 0, s, L.n, sc, L.minv, h->om + l);
@@ -1623,8 +1692,7 @@ hipError_t update_typed(fem_amg* h, const RV* K, hipStream_t s) {
 template <typename RV>
 void launch_post(const Level& L, const RV* vals, const double* x, const double* b, double* out, const int32_t* fl,
                  hipStream_t s) {
-    const unsigned nb = std::min<unsigned>(kPostGrid, blocks_for((int64_t)L.n * kLanes));
-    hipLaunchKernelGGL(post_kernel<RV>, dim3(nb), dim3(256), 0, s, L.n, L.row_ptr, L.ncol, vals, x, b, L.minv, out, fl);
+    FEM_PRODUCT(post_kernel, RV, product_grid<RV>(L.n, kNoCap), L.n, L.row_ptr, L.ncol, vals, x, b, L.minv, out, fl);
 }
 
 // out = x + M_l (b - A_l x) on level l (the finest level reads K)
@@ -1674,6 +1742,16 @@ bool krylov_level(const fem_amg* h, int c, int t) {
     return h->cycle == FEM_AMG_CYCLE_K && c >= 1 && c < t && c < h->nl - 1 && h->L[c].n >= h->kmin;
 }
 
+template <int STEP>
+void launch_kstep(const Level& C, const double* c, unsigned ng, const int32_t* fl, hipStream_t s) {
+    if (C.n > kStagedMin)
+        hipLaunchKernelGGL((kstep_product<STEP, true>), dim3(ng), dim3(256), 0, s, C.n, C.row_ptr, C.ncol,
+                           (const float*)C.vals, c, (const double*)C.b, C.kv1, C.kpart, fl);
+    else
+        hipLaunchKernelGGL((kstep_product<STEP, false>), dim3(ng), dim3(256), 0, s, C.n, C.row_ptr, C.ncol,
+                           (const float*)C.vals, c, (const double*)C.b, C.kv1, C.kpart, fl);
+}
+
 // The cycle from level l down: on entry bl is level l's right-hand side and
 // L[l].x its first sweep M_l bl; the result is written to out (levels above
 // the tail; at the tail start and below, the tail's own buffers) and
@@ -1718,36 +1796,41 @@ const double* cycle_from(fem_amg* h, int l, const double* bl, double* out, int t
     // residual, restriction and the first sweep of level c
     const int c = l + 1;
     Level& C = L[c];
-    if (l > 0)
-        hipLaunchKernelGGL(resid_restrict_kernel<float>, dim3(C.n), dim3(256), 0, s, C.mptr, C.mem, L[l].mask,
-                           L[l].row_ptr, L[l].ncol, (const float*)L[l].vals, L[l].x, bl, C.minv, C.b, C.x, fl);
-    else if (h->prec == FEM_FP64)
-        hipLaunchKernelGGL(resid_restrict_kernel<double>, dim3(C.n), dim3(256), 0, s, C.mptr, C.mem, L[0].mask,
-                           L[0].row_ptr, L[0].ncol, static_cast<const double*>(h->K), L[0].x, bl, C.minv, C.b, C.x,
-                           fl);
-    else
-        hipLaunchKernelGGL(resid_restrict_kernel<float>, dim3(C.n), dim3(256), 0, s, C.mptr, C.mem, L[0].mask,
-                           L[0].row_ptr, L[0].ncol, static_cast<const float*>(h->K), L[0].x, bl, C.minv, C.b, C.x,
-                           fl);
+    const Level& F = L[l];
+    if (F.n > kFuseNodes) {
+        if (l == 0 && h->prec == FEM_FP64)
+            FEM_PRODUCT(resid_kernel, double, product_grid<double>(F.n, kNoCap), F.n, F.row_ptr, F.ncol,
+                        static_cast<const double*>(h->K), F.x, bl, F.mask, F.r, fl);
+        else
+            FEM_PRODUCT(resid_kernel, float, product_grid<float>(F.n, kNoCap), F.n, F.row_ptr, F.ncol,
+                        l == 0 ? static_cast<const float*>(h->K) : (const float*)F.vals, F.x, bl, F.mask, F.r, fl);
+        hipLaunchKernelGGL(restrict_kernel, dim3(blocks_for(C.n)), dim3(256), 0, s, C.n, C.mptr, C.mem, F.r, C.minv,
+                           C.b, C.x, fl);
+    } else if (l == 0 && h->prec == FEM_FP64) {
+        hipLaunchKernelGGL(resid_restrict_kernel<double>, dim3(C.n), dim3(256), 0, s, C.mptr, C.mem, F.mask,
+                           F.row_ptr, F.ncol, static_cast<const double*>(h->K), F.x, bl, C.minv, C.b, C.x, fl);
+    } else {
+        hipLaunchKernelGGL(resid_restrict_kernel<float>, dim3(C.n), dim3(256), 0, s, C.mptr, C.mem, F.mask,
+                           F.row_ptr, F.ncol, l == 0 ? static_cast<const float*>(h->K) : (const float*)F.vals, F.x,
+                           bl, C.minv, C.b, C.x, fl);
+    }
     const unsigned nf = blocks_for(L[l].n);
     const unsigned nbp = std::min<unsigned>(kPostGrid, blocks_for((int64_t)L[l].n * kLanes));
     const bool fuse = l > 0 && C.aggm;
     if (krylov_level(h, c, t)) {
-        const unsigned ng = std::min<unsigned>(kPostGrid, blocks_for((int64_t)C.n * kLanes));
+        const unsigned ng = product_grid<float>(C.n, kPostGrid);
         const unsigned nu = blocks_for(C.n);
         const bool own1 = (int64_t)nu * ng <= kFusePartials;
         const bool own2 = (int64_t)(fuse ? nbp : nf) * ng <= kFusePartials;
         const int np1 = own1 ? (int)ng : 0, np2 = own2 ? (int)ng : 0;
         const double* part = C.kpart;
         cycle_from(h, c, C.b, C.kc1, t, fl, s);
-        hipLaunchKernelGGL(kstep_product<1>, dim3(ng), dim3(256), 0, s, C.n, C.row_ptr, C.ncol,
-                           (const float*)C.vals, (const double*)C.kc1, (const double*)C.b, C.kv1, C.kpart, fl);
+        launch_kstep<1>(C, C.kc1, ng, fl, s);
         if (!own1) hipLaunchKernelGGL(kstep_scalars<1>, dim3(1), dim3(256), 0, s, (int)ng, part, C.ksc, fl);
         hipLaunchKernelGGL(kstep_update, dim3(nu), dim3(256), 0, s, C.n, (const double*)C.kv1, np1, part, C.ksc,
                            (const double*)C.minv, C.b, C.x, fl);
         cycle_from(h, c, C.b, C.y, t, fl, s);
-        hipLaunchKernelGGL(kstep_product<2>, dim3(ng), dim3(256), 0, s, C.n, C.row_ptr, C.ncol,
-                           (const float*)C.vals, (const double*)C.y, (const double*)C.b, C.kv1, C.kpart, fl);
+        launch_kstep<2>(C, C.y, ng, fl, s);
         if (!own2) hipLaunchKernelGGL(kstep_scalars<2>, dim3(1), dim3(256), 0, s, (int)ng, part, C.ksc, fl);
         if (fuse) {
             hipLaunchKernelGGL(post_prolong_kernel<true>, dim3(nbp), dim3(256), 0, s, L[l].n, L[l].row_ptr, L[l].ncol,

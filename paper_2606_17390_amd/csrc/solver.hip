@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "block_rows.h"
 #include "fem_internal.h"
 
 namespace fem {
@@ -190,53 +191,43 @@ __device__ inline double sum_parts(const double* __restrict__ part, int n) {
 // y = K x on node blocks with the fused partial dot products
 //   ND >= 1: part0[block] = sum of w . y over the block's rows
 //   ND == 2: part1[block] = sum of y . y
-// 32 lanes per node, lane k takes the 3x3 blocks k, k + 32 of the node's rows;
-// fixed grid kSpmvGrid, 8 nodes per block and round.  Skipped when the stop
-// flag is set (if `fl` is given).
-template <typename RV, int ND>
-__global__ __launch_bounds__(256) void spmv_dot_kernel(int32_t n_nodes, const int32_t* __restrict__ row_ptr,
+// Skipped when the stop flag is
+// set (if `fl` is given).
+template <int ND>
+struct DotEpilogue {
+    const double* w;
+    double* y;
+    double d0, d1;
+    struct Data {
+        double w;
+    };
+    __device__ __forceinline__ Data load(int64_t I, int l) const { return {ND >= 1 ? w[3 * I + l] : 0.0}; }
+    __device__ __forceinline__ void finish(int64_t I, int l, const Data& d, const double s[3]) {
+        if (l < 3) {
+            const double yl = l == 0 ? s[0] : (l == 1 ? s[1] : s[2]);
+            y[3 * I + l] = yl;
+            if (ND >= 1) d0 += d.w * yl;
+            if (ND == 2) d1 += yl * yl;
+        }
+    }
+};
+
+template <typename RV, int ND, bool STAGED>
+__global__ __launch_bounds__(256, 4) void spmv_dot_kernel(int32_t n_nodes, const int32_t* __restrict__ row_ptr,
                                                        const int32_t* __restrict__ ncol,
                                                        const RV* __restrict__ val, const double* __restrict__ x,
                                                        double* __restrict__ y, const double* __restrict__ w,
                                                        double* __restrict__ part0, double* __restrict__ part1,
                                                        const int32_t* __restrict__ fl) {
     if (fl && fl[F_STOP]) return;
-    const int l = (int)(threadIdx.x & (kSpmvLanes - 1));
-    double d0 = 0.0, d1 = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * 8; base < n_nodes; base += (int64_t)kSpmvGrid * 8) {
-        const int64_t node = base + (threadIdx.x >> 5);
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        if (node < n_nodes) {
-            const int32_t b = row_ptr[3 * node], len = row_ptr[3 * node + 1] - b, deg = len / 3;
-            const int32_t* __restrict__ nc = ncol + b / 9;
-            for (int32_t k = l; k < deg; k += kSpmvLanes) {
-                const int64_t J = nc[k];
-                const double x0 = x[3 * J], x1 = x[3 * J + 1], x2 = x[3 * J + 2];
-                const RV* __restrict__ v = val + b + 3 * k;
-                s0 += (double)v[0] * x0 + (double)v[1] * x1 + (double)v[2] * x2;
-                s1 += (double)v[len] * x0 + (double)v[len + 1] * x1 + (double)v[len + 2] * x2;
-                s2 += (double)v[2 * len] * x0 + (double)v[2 * len + 1] * x1 + (double)v[2 * len + 2] * x2;
-            }
-        }
-#pragma unroll
-        for (int m = 1; m < kSpmvLanes; m <<= 1) {
-            s0 += __shfl_xor(s0, m, kSpmvLanes);
-            s1 += __shfl_xor(s1, m, kSpmvLanes);
-            s2 += __shfl_xor(s2, m, kSpmvLanes);
-        }
-        if (node < n_nodes && l < 3) {
-            const double yl = l == 0 ? s0 : (l == 1 ? s1 : s2);
-            y[3 * node + l] = yl;
-            if (ND >= 1) d0 += w[3 * node + l] * yl;
-            if (ND == 2) d1 += yl * yl;
-        }
-    }
+    DotEpilogue<ND> e{w, y, 0.0, 0.0};
+    block_rows<RV, STAGED>(n_nodes, row_ptr, ncol, val, x, e);
     if (ND >= 1) {
-        const double t0 = block_sum(d0);
+        const double t0 = block_sum(e.d0);
         if (threadIdx.x == 0) part0[blockIdx.x] = t0;
     }
     if (ND == 2) {
-        const double t1 = block_sum(d1);
+        const double t1 = block_sum(e.d1);
         if (threadIdx.x == 0) part1[blockIdx.x] = t1;
     }
 }
@@ -829,16 +820,28 @@ hipError_t spmv(const fem_csr* csr, const void* vals, fem_precision prec, const 
     return hipGetLastError();
 }
 
+// With dot products the grid is kSpmvGrid (the partials the reductions read).
+template <typename RV, int ND>
+void launch_spmv_dot(int32_t nn, const int32_t* row_ptr, const int32_t* ncol, const RV* vals, const double* x, double* y,
+                     const double* w, double* part0, double* part1, const int32_t* fl, hipStream_t s) {
+    const bool staged = nn > kStagedMin;
+    const unsigned nb = ND > 0 ? (unsigned)kSpmvGrid : row_blocks(nn, staged, kStagedNodes<RV>, 1u << 30);
+    if (staged)
+        hipLaunchKernelGGL((spmv_dot_kernel<RV, ND, true>), dim3(nb), dim3(256), 0, s, nn, row_ptr, ncol, vals, x, y, w,
+                           part0, part1, fl);
+    else
+        hipLaunchKernelGGL((spmv_dot_kernel<RV, ND, false>), dim3(nb), dim3(256), 0, s, nn, row_ptr, ncol, vals, x, y, w,
+                           part0, part1, fl);
+}
+
 template <int ND>
 void spmv_dot(const fem_csr* csr, const int32_t* ncol, const void* vals, fem_precision prec, const double* x,
               double* y, const double* w, double* part0, double* part1, const int32_t* fl, hipStream_t s) {
     const int32_t nn = csr->n_rows / 3;
     if (prec == FEM_FP64)
-        hipLaunchKernelGGL((spmv_dot_kernel<double, ND>), dim3(kSpmvGrid), dim3(256), 0, s, nn, csr->row_ptr, ncol,
-                           static_cast<const double*>(vals), x, y, w, part0, part1, fl);
+        launch_spmv_dot<double, ND>(nn, csr->row_ptr, ncol, static_cast<const double*>(vals), x, y, w, part0, part1, fl, s);
     else
-        hipLaunchKernelGGL((spmv_dot_kernel<float, ND>), dim3(kSpmvGrid), dim3(256), 0, s, nn, csr->row_ptr, ncol,
-                           static_cast<const float*>(vals), x, y, w, part0, part1, fl);
+        launch_spmv_dot<float, ND>(nn, csr->row_ptr, ncol, static_cast<const float*>(vals), x, y, w, part0, part1, fl, s);
 }
 
 int check_csr(const fem_csr* csr, const void* vals, const char* who) {
@@ -932,6 +935,7 @@ int krylov_solve(const char* who, const fem_csr* csr, const void* K_vals, fem_pr
     WsCarver c(ws, ws_bytes);
     SolverWs w;
     carve_solver(c, n, csr->nnz, &w);
+    if (csr->nnz == 0) K_vals = w.minv;  // no entries: the products still need an address they may read
     const unsigned nbl = (unsigned)(((int64_t)nn * kSpmvLanes + 255) / 256);
     const unsigned nbn = (unsigned)(((int64_t)nn + 255) / 256);
     const int block = pc == FEM_PC_BLOCK_JACOBI ? 1 : 0;
