@@ -167,18 +167,15 @@ __global__ __launch_bounds__(256) void precond_kernel(int32_t n_nodes, const int
     for (int k = 0; k < 9; ++k) minv[9 * I + k] = M[k];
 }
 
-// Fixed-order block sum of one value per thread (256 threads); every thread
-// gets the result.
+// Fixed-order block sum of one value per thread (256 threads), in every
+// thread: the two halves of each wave, then the eight sums.
 __device__ inline double block_sum(double v) {
-    __shared__ double sh[256];
+    __shared__ double sh[8];
+    v = sum32(v);
     __syncthreads();
-    sh[threadIdx.x] = v;
+    if ((threadIdx.x & 31) == 0) sh[threadIdx.x >> 5] = v;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    return sh[0];
+    return ((sh[0] + sh[1]) + (sh[2] + sh[3])) + ((sh[4] + sh[5]) + (sh[6] + sh[7]));
 }
 
 // Second stage: the sum of n partials in a fixed order (one 256-thread block).
@@ -567,13 +564,152 @@ __global__ __launch_bounds__(256) void dot_kernel(int64_t n, const double* __res
 // it had no step (F_J = 0).
 constexpr int kGmresM = FEM_GMRES_RESTART;
 
-// v = scale v (scale = sc[S_BETA]); mx = M0 v (node blocks)
-__global__ __launch_bounds__(256) void gm_normalize(int32_t n_nodes, double* __restrict__ v,
-                                                    const double* __restrict__ minv, double* __restrict__ mx,
-                                                    const double* __restrict__ sc, const int32_t* __restrict__ fl) {
+// The Gram-Schmidt kernels: a workgroup takes pieces of 256 PER entries, PER
+// per thread, held in registers while the basis vectors stream by four at a
+// time.  PER is 1 up to 65,536 unknowns (latency: as many workgroups as there
+// are), then 4.  Per step, on average over a solve of the 100^3 system: dots
+// 96 -> 59 us, update 79 -> 64 us (one vector after the other before; with 12
+// entries per thread 135 us, for want of waves).
+inline int gs_per(int64_t n) { return n <= 65536 ? 1 : 4; }
+inline int gs_blocks(int64_t n) {
+    const int64_t piece = 256 * gs_per(n);
+    return (int)std::min<int64_t>(kGrid, (n + piece - 1) / piece);
+}
+// Up to this many workgroups the update sums their partial products itself
+// (31 x 128 values per workgroup at most), which saves a launch; above, a
+// kernel of its own does (4.7 us against 16 MB and more of re-reads).
+constexpr int kGsFuse = 128;
+
+// hpart[i][block] = partial of (w, v_i), i = 0..j.  Bound by HBM on a large
+// system (w once, then j + 1 basis vectors): the block's entries of w stay in
+// registers and the sums of a wave in LDS, so the only barrier is the last.
+template <int PER>
+__device__ __forceinline__ void gs_dots(int64_t n, int j, const double* __restrict__ V, int64_t ldv,
+                                        const double* __restrict__ w, double (*sh)[8]) {
+    constexpr int64_t piece = 256 * PER;
+    const int half = (int)(threadIdx.x >> 5);
+    bool first = true;
+    for (int64_t p0 = (int64_t)blockIdx.x * piece; p0 < n; p0 += (int64_t)gridDim.x * piece, first = false) {
+        double wr[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int64_t k = p0 + q * 256 + threadIdx.x;
+            wr[q] = k < n ? w[k] : 0.0;
+        }
+        for (int i = 0; i <= j; i += 4) {  // four vectors at a time (past the last: it again, not stored)
+            double v[4][PER], d[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double* __restrict__ vi = V + (int64_t)min(i + u, j) * ldv;
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    const int64_t k = p0 + q * 256 + threadIdx.x;
+                    v[u][q] = vi[k < n ? k : n - 1];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                d[u] = 0.0;
+#pragma unroll
+                for (int q = 0; q < PER; ++q) d[u] += wr[q] * v[u][q];
+                d[u] = sum32(d[u]);
+                if ((threadIdx.x & 31) == 0 && i + u <= j) sh[i + u][half] = first ? d[u] : sh[i + u][half] + d[u];
+            }
+        }
+    }
+}
+
+template <int PER>
+__global__ __launch_bounds__(256) void gm_dots(int64_t n, int j, const double* __restrict__ V, int64_t ldv,
+                                               const double* __restrict__ w, double* __restrict__ hpart,
+                                               const int32_t* __restrict__ fl) {
     if (fl[0]) return;
-    const double scale = sc[S_BETA];
-    for (int64_t I = (int64_t)blockIdx.x * 256 + threadIdx.x; I < n_nodes; I += (int64_t)kGrid * 256) {
+    __shared__ double sh[kGmresM][8];
+    gs_dots<PER>(n, j, V, ldv, w, sh);
+    __syncthreads();
+    const int i = (int)threadIdx.x;
+    if (i <= j)
+        hpart[(int64_t)i * kGrid + blockIdx.x] =
+            ((sh[i][0] + sh[i][1]) + (sh[i][2] + sh[i][3])) + ((sh[i][4] + sh[i][5]) + (sh[i][6] + sh[i][7]));
+}
+
+// H(i, j) = sum of the nb partials hpart[i][*], one block per i
+__global__ __launch_bounds__(256) void gm_hreduce(const double* __restrict__ hpart, int nb, int j,
+                                                  double* __restrict__ H, const int32_t* __restrict__ fl) {
+    if (fl[0]) return;
+    const int i = blockIdx.x;
+    const double t = sum_parts(hpart + (int64_t)i * kGrid, nb);
+    if (threadIdx.x == 0) H[(int64_t)j * (kGmresM + 1) + i] = t;
+}
+
+// w -= sum_i H(i, j) v_i; part0 = partials of (w, w).  np > 0: column j of H
+// from the np partials hpart first (block 0 stores it).
+template <int PER>
+__global__ __launch_bounds__(256) void gm_update(int64_t n, int j, const double* __restrict__ V, int64_t ldv, int np,
+                                                 const double* __restrict__ hpart, double* __restrict__ H,
+                                                 double* __restrict__ w, double* __restrict__ part0,
+                                                 const int32_t* __restrict__ fl) {
+    if (fl[0]) return;
+    __shared__ double h[kGmresM];
+    if (np > 0) {
+        // 8 lanes per column entry
+        const int i = (int)(threadIdx.x >> 3);
+        double t = 0.0;
+        if (i <= j)
+            for (int k = (int)(threadIdx.x & 7); k < np; k += 8) t += hpart[(int64_t)i * kGrid + k];
+        t = sum_lanes<8>(t);
+        if (i <= j && (threadIdx.x & 7) == 0) {
+            h[i] = t;
+            if (blockIdx.x == 0) H[(int64_t)j * (kGmresM + 1) + i] = t;
+        }
+    } else if ((int)threadIdx.x <= j) {
+        h[threadIdx.x] = H[(int64_t)j * (kGmresM + 1) + threadIdx.x];
+    }
+    __syncthreads();
+    constexpr int64_t piece = 256 * PER;
+    double d = 0.0;
+    for (int64_t p0 = (int64_t)blockIdx.x * piece; p0 < n; p0 += (int64_t)gridDim.x * piece) {
+        double wr[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int64_t k = p0 + q * 256 + threadIdx.x;
+            wr[q] = w[k < n ? k : n - 1];
+        }
+        for (int i = 0; i <= j; i += 4) {  // four vectors at a time (past the last: it again, times zero)
+            double v[4][PER], hi[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double* __restrict__ vi = V + (int64_t)min(i + u, j) * ldv;
+                hi[u] = i + u <= j ? h[i + u] : 0.0;
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    const int64_t k = p0 + q * 256 + threadIdx.x;
+                    v[u][q] = vi[k < n ? k : n - 1];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int q = 0; q < PER; ++q) wr[q] -= hi[u] * v[u][q];
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int64_t k = p0 + q * 256 + threadIdx.x;
+            if (k < n) {
+                w[k] = wr[q];
+                d += wr[q] * wr[q];
+            }
+        }
+    }
+    const double t = block_sum(d);
+    if (threadIdx.x == 0) part0[blockIdx.x] = t;
+}
+
+// v = scale v; mx = M0 v (node blocks), this workgroup's share
+__device__ __forceinline__ void gm_normalize_rows(int32_t n_nodes, double scale, int64_t block, int64_t blocks,
+                                                  double* __restrict__ v, const double* __restrict__ minv,
+                                                  double* __restrict__ mx) {
+    for (int64_t I = block * 256 + threadIdx.x; I < n_nodes; I += blocks * 256) {
         double q[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -584,69 +720,59 @@ __global__ __launch_bounds__(256) void gm_normalize(int32_t n_nodes, double* __r
     }
 }
 
-// hpart[i][block] = partial of (w, v_i), i = 0..j
-__global__ __launch_bounds__(256) void gm_dots(int64_t n, int j, const double* __restrict__ V, int64_t ldv,
-                                               const double* __restrict__ w, double* __restrict__ hpart,
-                                               const int32_t* __restrict__ fl) {
+// first vector of a cycle (scale = sc[S_BETA])
+__global__ __launch_bounds__(256) void gm_normalize(int32_t n_nodes, double* __restrict__ v,
+                                                    const double* __restrict__ minv, double* __restrict__ mx,
+                                                    const double* __restrict__ sc, const int32_t* __restrict__ fl) {
     if (fl[0]) return;
-    for (int i = 0; i <= j; ++i) {
-        const double* __restrict__ vi = V + (int64_t)i * ldv;
-        double d = 0.0;
-        for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)kGrid * 256) d += w[k] * vi[k];
-        const double t = block_sum(d);
-        if (threadIdx.x == 0) hpart[(int64_t)i * kGrid + blockIdx.x] = t;
-    }
+    gm_normalize_rows(n_nodes, sc[S_BETA], (int64_t)blockIdx.x, (int64_t)gridDim.x, v, minv, mx);
 }
 
-// H(i, j) = sum of hpart[i][*], one block per i
-__global__ __launch_bounds__(256) void gm_hreduce(const double* __restrict__ hpart, int j, double* __restrict__ H,
-                                                  const int32_t* __restrict__ fl) {
-    if (fl[0]) return;
-    const int i = blockIdx.x;
-    const double t = sum_parts(hpart + (int64_t)i * kGrid, kGrid);
-    if (threadIdx.x == 0) H[(int64_t)j * (kGmresM + 1) + i] = t;
-}
-
-// w -= sum_i H(i, j) v_i; part0 = partials of (w, w)
-__global__ __launch_bounds__(256) void gm_update(int64_t n, int j, const double* __restrict__ V, int64_t ldv,
-                                                 const double* __restrict__ H, double* __restrict__ w,
-                                                 double* __restrict__ part0, const int32_t* __restrict__ fl) {
-    if (fl[0]) return;
-    const double* __restrict__ h = H + (int64_t)j * (kGmresM + 1);
-    double d = 0.0;
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)kGrid * 256) {
-        double wk = w[k];
-        for (int i = 0; i <= j; ++i) wk -= h[i] * V[(int64_t)i * ldv + k];
-        w[k] = wk;
-        d += wk * wk;
-    }
-    const double t = block_sum(d);
-    if (threadIdx.x == 0) part0[blockIdx.x] = t;
-}
-
-// End of step j: H(j+1, j) = ||w||, the earlier rotations applied to column
-// j, a new rotation zeroing H(j+1, j), g rotated; |g(j+1)| / ||b|| is the
-// residual of the cycle's least-squares solution.  The cycle ends on
-// convergence, a breakdown (H(j+1, j) = 0: the solution is in the space),
-// a non-finite value, the iteration limit or after kGmresM steps.
-__global__ __launch_bounds__(256) void gm_finish(const double* __restrict__ part0, int j, double* __restrict__ H,
-                                                 double* __restrict__ cs, double* __restrict__ sn,
-                                                 double* __restrict__ g, double* __restrict__ sc,
-                                                 int32_t* __restrict__ fl, double rtol, int32_t max_iter) {
-    if (fl[F_CYC]) return;
-    const double ww = sum_parts(part0, kGrid);
-    if (threadIdx.x != 0) return;
+// End of step j: H(j+1, j) = ||w|| from the nb partials, the earlier rotations
+// applied to column j, a new rotation zeroing H(j+1, j), g rotated;
+// |g(j+1)| / ||b|| is the residual of the cycle's least-squares solution.  The
+// cycle ends on convergence, a breakdown (H(j+1, j) = 0: the solution is in
+// the space), a non-finite value, the iteration limit or after kGmresM steps.
+// Workgroup 0 does this while the others, each from the same sum of the
+// partials, normalise v = w for the next step (mx = M0 v), so that step waits
+// for one launch instead of two.  A workgroup that sees the cycle ended, by
+// this step or an earlier one, leaves: a cycle that has ended takes no next
+// vector.
+__global__ __launch_bounds__(256) void gm_finish(const double* __restrict__ part0, int nb, int j,
+                                                 double* __restrict__ H, double* __restrict__ cs,
+                                                 double* __restrict__ sn, double* __restrict__ g,
+                                                 double* __restrict__ sc, int32_t* __restrict__ fl, double rtol,
+                                                 int32_t max_iter, int32_t n_nodes, double* __restrict__ v,
+                                                 const double* __restrict__ minv, double* __restrict__ mx) {
+    __shared__ int ended;
+    __shared__ double hs[kGmresM + 1], cr[kGmresM], sr[kGmresM];
+    const int t = (int)threadIdx.x;
+    if (t == 0) ended = __hip_atomic_load(fl + F_CYC, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     double* h = H + (int64_t)j * (kGmresM + 1);
-    const double hn = sqrt(ww);
-    h[j + 1] = hn;
-    for (int i = 0; i < j; ++i) {
-        const double a = h[i], b = h[i + 1];
-        h[i] = cs[i] * a + sn[i] * b;
-        h[i + 1] = -sn[i] * a + cs[i] * b;
+    if (blockIdx.x == 0 && t <= j) {
+        hs[t] = h[t];
+        if (t < j) {
+            cr[t] = cs[t];
+            sr[t] = sn[t];
+        }
     }
-    const double a = h[j], b = h[j + 1];
-    const double r = hypot(a, b);
-    const double c = r > 0.0 ? a / r : 1.0, sgn = r > 0.0 ? b / r : 0.0;
+    __syncthreads();
+    if (ended) return;
+    const double hn = sqrt(sum_parts(part0, nb));
+    if (blockIdx.x != 0) {
+        gm_normalize_rows(n_nodes, hn > 0.0 ? 1.0 / hn : 0.0, (int64_t)blockIdx.x - 1, (int64_t)gridDim.x - 1, v,
+                          minv, mx);
+        return;
+    }
+    if (t != 0) return;
+    double a = hs[0];
+    for (int i = 0; i < j; ++i) {
+        const double b = hs[i + 1];
+        h[i] = cr[i] * a + sr[i] * b;
+        a = -sr[i] * a + cr[i] * b;
+    }
+    const double r = hypot(a, hn);
+    const double c = r > 0.0 ? a / r : 1.0, sgn = r > 0.0 ? hn / r : 0.0;
     cs[j] = c;
     sn[j] = sgn;
     h[j] = r;
@@ -654,39 +780,52 @@ __global__ __launch_bounds__(256) void gm_finish(const double* __restrict__ part
     const double gj = g[j];
     g[j] = c * gj;
     g[j + 1] = -sgn * gj;
-    const double bn = sqrt(sc[S_BB]);
-    const double res = bn > 0.0 ? fabs(g[j + 1]) / bn : fabs(g[j + 1]);
+    const double bn = sqrt(sc[S_BB]), gn = fabs(sgn * gj);
+    const double res = bn > 0.0 ? gn / bn : gn;
     const int32_t it = fl[F_ITER] + 1;
     fl[F_ITER] = it;
     fl[F_J] = j + 1;
     sc[S_RES] = res;
-    sc[S_BETA] = hn > 0.0 ? 1.0 / hn : 0.0;
     const bool stop = res <= rtol || !isfinite(res) || hn == 0.0 || !(r > 0.0) || it >= max_iter;
     if (stop) fl[F_STOP] = 1;
-    if (stop || j + 1 == kGmresM) fl[F_CYC] = 1;
+    if (stop || j + 1 == kGmresM) __hip_atomic_store(fl + F_CYC, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// y = R^-1 g over the cycle's F_J steps (upper triangular H), one thread
-__global__ void gm_solve_y(const double* __restrict__ H, const double* __restrict__ g, double* __restrict__ y,
-                           const int32_t* __restrict__ fl) {
-    const int m = fl[F_J];
-    for (int i = m - 1; i >= 0; --i) {
-        double t = g[i];
-        for (int k = i + 1; k < m; ++k) t -= H[(int64_t)k * (kGmresM + 1) + i] * y[k];
-        const double d = H[(int64_t)i * (kGmresM + 1) + i];
-        y[i] = d != 0.0 ? t / d : 0.0;
+// y = R^-1 g over the cycle's F_J steps (upper triangular H), one wave: column
+// by column from LDS, lane i holding entry i
+__global__ __launch_bounds__(64) void gm_solve_y(const double* __restrict__ H, const double* __restrict__ g,
+                                                 double* __restrict__ y, const int32_t* __restrict__ fl) {
+    __shared__ double h[kGmresM][kGmresM + 1];
+    const int m = fl[F_J], t = (int)threadIdx.x;
+    for (int i = t; i < m * (kGmresM + 1); i += 64) h[i / (kGmresM + 1)][i % (kGmresM + 1)] = H[i];
+    __syncthreads();
+    double r = t < m ? g[t] : 0.0;
+    for (int k = m - 1; k >= 0; --k) {
+        const double d = h[k][k];
+        const double yk = d != 0.0 ? __shfl(r, k, 64) / d : 0.0;
+        if (t < k) r -= h[k][t] * yk;
+        if (t == k) y[k] = yk;
     }
 }
 
-// u = sum_{i < F_J} y_i v_i (zero if the cycle had no step)
+// u = sum_{i < F_J} y_i v_i (add: u += ...; no step: zero, or u as it is),
+// four vectors at a time
 __global__ __launch_bounds__(256) void gm_combine(int64_t n, const double* __restrict__ V, int64_t ldv,
-                                                  const double* __restrict__ y, double* __restrict__ u,
+                                                  const double* __restrict__ y, int add, double* __restrict__ u,
                                                   const int32_t* __restrict__ fl) {
     const int m = fl[F_J];
     for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)kGrid * 256) {
         double t = 0.0;
-        for (int i = 0; i < m; ++i) t += y[i] * V[(int64_t)i * ldv + k];
-        u[k] = t;
+        int i = 0;
+        for (; i + 4 <= m; i += 4) {
+            double v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = V[(int64_t)(i + q) * ldv + k];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t += y[i + q] * v[q];
+        }
+        for (; i < m; ++i) t += y[i] * V[(int64_t)i * ldv + k];
+        u[k] = add ? u[k] + t : t;
     }
 }
 
@@ -904,6 +1043,17 @@ extern "C" int fem_csr_transpose(const fem_csr* csr, const void* K_vals, fem_pre
 
 namespace {
 
+// w = K z_j made orthogonal to v_0, ..., v_j: column j of H, w updated,
+// partials of ||w||^2
+template <int PER>
+void gram_schmidt(int64_t n, int j, int nb, bool fuse, const GmresWs& g, double* w, double* part0, const int32_t* cyc,
+                  hipStream_t s) {
+    hipLaunchKernelGGL(gm_dots<PER>, dim3(nb), dim3(256), 0, s, n, j, g.V, g.ldv, w, g.hpart, cyc);
+    if (!fuse) hipLaunchKernelGGL(gm_hreduce, dim3(j + 1), dim3(256), 0, s, g.hpart, nb, j, g.H, cyc);
+    hipLaunchKernelGGL(gm_update<PER>, dim3(nb), dim3(256), 0, s, n, j, g.V, g.ldv, fuse ? nb : 0, g.hpart, g.H, w,
+                       part0, cyc);
+}
+
 // The Krylov iterations of fem_solve (amg NULL: Jacobi or block Jacobi by pc)
 // and fem_solve_amg (M = one V-cycle of amg).
 int krylov_solve(const char* who, const fem_csr* csr, const void* K_vals, fem_precision prec, fem_krylov method,
@@ -985,21 +1135,24 @@ int krylov_solve(const char* who, const fem_csr* csr, const void* K_vals, fem_pr
             return e;
         };
         FEM_HIP_CHECK(read_back());
+        const int per = gs_per(n), ngs = gs_blocks(n);
+        const bool fuse = ngs <= kGsFuse;
+        const unsigned nnb = std::min<unsigned>(kGrid, nbn);
         while (!flh[F_STOP]) {
             for (int j = 0; j < kGmresM; ++j) {
                 double* vj = g.V + (int64_t)j * g.ldv;
                 double* vn = g.V + (int64_t)(j + 1) * g.ldv;
                 double* zj = flex ? g.Z + (int64_t)j * g.ldv : w.ph;
-                hipLaunchKernelGGL(gm_normalize, dim3(kGrid), dim3(256), 0, s, nn, vj, minv, amg ? mx : zj, w.sc,
-                                   cyc);
+                double* zn = flex && j + 1 < kGmresM ? zj + g.ldv : w.ph;  // M0 of the next vector (no multigrid)
+                if (j == 0)
+                    hipLaunchKernelGGL(gm_normalize, dim3(nnb), dim3(256), 0, s, nn, vj, minv, amg ? mx : zj, w.sc,
+                                       cyc);
                 if (amg) FEM_HIP_CHECK(amg_apply_cycle(amg, vj, zj, true, cyc, s));
                 spmv_dot<0>(csr, w.ncol, K_vals, prec, zj, vn, nullptr, nullptr, nullptr, cyc, s);
-                hipLaunchKernelGGL(gm_dots, dim3(kGrid), dim3(256), 0, s, (int64_t)n, j, g.V, g.ldv, vn, g.hpart, cyc);
-                hipLaunchKernelGGL(gm_hreduce, dim3(j + 1), dim3(256), 0, s, g.hpart, j, g.H, cyc);
-                hipLaunchKernelGGL(gm_update, dim3(kGrid), dim3(256), 0, s, (int64_t)n, j, g.V, g.ldv, g.H, vn,
-                                   w.part0, cyc);
-                hipLaunchKernelGGL(gm_finish, dim3(1), dim3(256), 0, s, w.part0, j, g.H, g.cs, g.sn, g.g, w.sc, w.fl,
-                                   rtol, max_iter);
+                if (per == 1) gram_schmidt<1>(n, j, ngs, fuse, g, vn, w.part0, cyc, s);
+                else gram_schmidt<4>(n, j, ngs, fuse, g, vn, w.part0, cyc, s);
+                hipLaunchKernelGGL(gm_finish, dim3(1 + nnb), dim3(256), 0, s, w.part0, ngs, j, g.H, g.cs, g.sn, g.g,
+                                   w.sc, w.fl, rtol, max_iter, nn, vn, minv, amg ? mx : zn);
                 // a multigrid step costs far more than a stream synchronisation:
                 // stop launching once the cycle has ended
                 if (amg) {
@@ -1009,19 +1162,19 @@ int krylov_solve(const char* who, const fem_csr* csr, const void* K_vals, fem_pr
                 }
             }
             // x += M (V y) (flexible: x += Z y); then the true residual of the restart
-            hipLaunchKernelGGL(gm_solve_y, dim3(1), dim3(1), 0, s, g.H, g.g, g.y, w.fl);
+            hipLaunchKernelGGL(gm_solve_y, dim3(1), dim3(64), 0, s, g.H, g.g, g.y, w.fl);
             if (flex) {
-                hipLaunchKernelGGL(gm_combine, dim3(kGrid), dim3(256), 0, s, (int64_t)n, g.Z, g.ldv, g.y, w.sh,
+                hipLaunchKernelGGL(gm_combine, dim3(kGrid), dim3(256), 0, s, (int64_t)n, g.Z, g.ldv, g.y, 1, x,
                                    w.fl);
             } else {
-                hipLaunchKernelGGL(gm_combine, dim3(kGrid), dim3(256), 0, s, (int64_t)n, g.V, g.ldv, g.y, w.p,
+                hipLaunchKernelGGL(gm_combine, dim3(kGrid), dim3(256), 0, s, (int64_t)n, g.V, g.ldv, g.y, 0, w.p,
                                    w.fl);
                 if (amg)
                     FEM_HIP_CHECK(amg_apply_cycle(amg, w.p, w.sh, false, nullptr, s));
                 else
                     hipLaunchKernelGGL(gm_apply_minv, dim3(kGrid), dim3(256), 0, s, nn, minv, w.p, w.sh);
+                hipLaunchKernelGGL(gm_addx, dim3(kGrid), dim3(256), 0, s, (int64_t)n, w.sh, x);
             }
-            hipLaunchKernelGGL(gm_addx, dim3(kGrid), dim3(256), 0, s, (int64_t)n, w.sh, x);
             spmv_dot<0>(csr, w.ncol, K_vals, prec, x, w.t, nullptr, nullptr, nullptr, stp, s);
             hipLaunchKernelGGL(gm_residual, dim3(kGrid), dim3(256), 0, s, (int64_t)n, b, w.t, g.V, w.part0, w.part1,
                                w.fl);

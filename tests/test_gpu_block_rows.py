@@ -71,3 +71,21 @@ def test_product_inside_a_solve(fem, name, dtype):
     if name in ("staged_ragged", "some_too_long"):
         y = fem.csr_spmv(csr, K, x)
         assert float((y - A @ x).norm() / y.norm()) <= 1e-13
+
+
+@pytest.mark.parametrize("method", ["gmres", "fgmres"])
+@pytest.mark.parametrize("n", [1, 85, 10922, 10923, 21845, 21846, 349526])
+def test_gram_schmidt_sizes(fem, n, method):
+    """GMRES around the lines of its vector kernels (one entry per thread up to
+    65,536 unknowns; the partial products summed by the update up to 128
+    workgroups; several pieces per workgroup past 1,048,576)."""
+    print(n, method, flush=True)
+    row_ptr, col, K = _system(n, np.full(n, min(n, 3)), torch.float64)
+    csr = fem.Csr(row_ptr, col, None, int(col.numel()), 3 * n, row_ptr, col)
+    b = torch.randn(3 * n, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    solver = fem.Solver(csr, "cuda", precond=fem.PC_JACOBI, method=method)
+    x, its, res = solver.solve(K, b, rtol=1e-10, max_iter=400)
+    y, _, _ = solver.solve(K, b, rtol=1e-10, max_iter=400)
+    A = torch.sparse_csr_tensor(row_ptr.long(), col.long(), K, size=(3 * n, 3 * n))
+    assert its > 1 and float((b - A @ x).norm() / b.norm()) <= 1e-9
+    assert torch.equal(x, y)
