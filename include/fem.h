@@ -336,8 +336,9 @@ int fem_residual_vjp_noalloc(const fem_mesh *mesh, const fem_batch *batch, const
  *            method))
  * The reductions are fixed-order (bitwise reproducible).  The iteration state
  * stays on the device; the host reads the stop flag once per 32 iterations
- * (4 with fem_solve_amg; GMRES: once per restart cycle, after every step
- * with fem_solve_amg), one stream synchronisation each.  A breakdown (a zero inner product) or
+ * (4 with fem_solve_amg; GMRES: once per restart cycle), one stream
+ * synchronisation each; with fem_solve_amg a GMRES step reports its end to
+ * pinned host memory and the host follows at most one step behind.  A breakdown (a zero inner product) or
  * a non-finite residual ends the iteration.  ||b - K x|| is the recursive
  * residual of the method.
  * Returns FEM_ENOCONV if rtol is not reached (x holds the last iterate).
@@ -418,8 +419,9 @@ int fem_csr_transpose(const fem_csr *csr, const void *K_vals, fem_precision prec
  *   uploaded.  bc_mask: device [n_rows] uint8, nonzero on constrained dofs
  *   (their rows of K are identity rows, as fem_residual_tangent writes
  *   them), or NULL (no constrained dofs).  The handle keeps csr's device
- *   pointers (they must stay valid) and owns device memory allocated here
- *   (freed by fem_amg_destroy); the coarse values are not computed yet
+ *   pointers (they must stay valid) and owns device memory, a few bytes of
+ *   pinned host memory and two events allocated here (freed by
+ *   fem_amg_destroy; one solve at a time uses them); the coarse values are not computed yet
  *   (fem_amg_update).  Synchronises `stream`.
  *   Errors: FEM_EINVAL (bad arguments, a node with more than 21845
  *   neighbours), FEM_ENOMEM (host or device allocation), FEM_EHIP.

@@ -140,6 +140,8 @@ struct fem_amg {
     int32_t kmin = 0;          // K-cycle steps on levels of at least this many nodes
     bool packed = false;       // the tail runs from its packed form
     fem::TailPacked* tail = nullptr;  // device: its arguments
+    fem::StepReport* reports = nullptr;  // pinned host memory, two slots
+    hipEvent_t ev[2] = {nullptr, nullptr};
     size_t tail_lds = 0;       // bytes of LDS it takes
 };
 
@@ -1726,6 +1728,8 @@ int amg_update(fem_amg* h, const void* K, fem_precision prec, hipStream_t s) {
 const double* amg_smoother0(const fem_amg* h) { return h->L[0].minv; }
 double* amg_level0_x(fem_amg* h) { return h->L[0].x; }
 fem_amg_cycle amg_cycle_type(const fem_amg* h) { return h->cycle; }
+StepReport* amg_reports(fem_amg* h) { return h->reports; }
+hipEvent_t amg_report_event(fem_amg* h, int slot) { return h->ev[slot]; }
 bool amg_matches(const fem_amg* h, const fem_csr* csr) {
     return h && csr && h->n_rows == csr->n_rows && h->nnz == csr->nnz && h->L[0].row_ptr == csr->row_ptr;
 }
@@ -1879,6 +1883,21 @@ hipError_t amg_apply_cycle(fem_amg* h, const double* b, double* z, bool presmoot
 }  // namespace fem
 
 using namespace fem;
+
+namespace {
+
+// Everything a handle owns, and the handle; the device of the allocations is
+// current.
+hipError_t free_handle(fem_amg* h) {
+    const hipError_t e = hipFree(h->mem);  // waits for the device
+    for (hipEvent_t ev : h->ev)
+        if (ev) (void)hipEventDestroy(ev);
+    if (h->reports) (void)hipHostFree(h->reports);
+    delete h;
+    return e;
+}
+
+}  // namespace
 
 extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precision prec, const uint8_t* bc_mask,
                               fem_amg** out, void* stream) {
@@ -2135,10 +2154,13 @@ extern "C" int fem_amg_create(const fem_csr* csr, const void* K_vals, fem_precis
     if (e == hipSuccess && packed)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(tail_packed_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTailLds);
+    if (e == hipSuccess)
+        e = hipHostMalloc(reinterpret_cast<void**>(&h->reports), 2 * sizeof(StepReport), hipHostMallocMapped);
+    for (hipEvent_t& ev : h->ev)
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e != hipSuccess || !cv.ok()) {
-        (void)hipFree(h->mem);
-        delete h;
-        return set_error(FEM_EHIP, "fem_amg_create: upload failed: %s", hipGetErrorString(e));
+        free_handle(h);
+        return set_error(FEM_EHIP, "fem_amg_create: set-up failed: %s", hipGetErrorString(e));
     }
     *out = h;
     return FEM_OK;
@@ -2238,10 +2260,10 @@ extern "C" int fem_amg_destroy(fem_amg* amg) {
     if (!amg) return FEM_OK;
     int cur = 0;
     (void)hipGetDevice(&cur);
-    if (cur != amg->device) (void)hipSetDevice(amg->device);
-    const hipError_t e = hipFree(amg->mem);
-    if (cur != amg->device) (void)hipSetDevice(cur);
-    delete amg;
+    const int own = amg->device;
+    if (cur != own) (void)hipSetDevice(own);
+    const hipError_t e = free_handle(amg);
+    if (cur != own) (void)hipSetDevice(cur);
     if (e != hipSuccess) return set_error(FEM_EHIP, "fem_amg_destroy: %s", hipGetErrorString(e));
     return FEM_OK;
 }

@@ -92,6 +92,15 @@ hipError_t amg_apply_cycle(fem_amg* h, const double* b, double* z, bool presmoot
 const double* amg_smoother0(const fem_amg* h);
 double* amg_level0_x(fem_amg* h);
 bool amg_matches(const fem_amg* h, const fem_csr* csr);
+// What the solver's steps report to the host, two steps in flight: pinned
+// host memory that the device writes, and an event per slot.  Owned by the
+// handle (one solve at a time).
+struct StepReport {
+    double res;
+    int32_t ended;
+};
+StepReport* amg_reports(fem_amg* h);
+hipEvent_t amg_report_event(fem_amg* h, int slot);
 fem_amg_cycle amg_cycle_type(const fem_amg* h);
 
 }  // namespace fem

@@ -743,7 +743,8 @@ __global__ __launch_bounds__(256) void gm_finish(const double* __restrict__ part
                                                  double* __restrict__ sn, double* __restrict__ g,
                                                  double* __restrict__ sc, int32_t* __restrict__ fl, double rtol,
                                                  int32_t max_iter, int32_t n_nodes, double* __restrict__ v,
-                                                 const double* __restrict__ minv, double* __restrict__ mx) {
+                                                 const double* __restrict__ minv, double* __restrict__ mx,
+                                                 StepReport* __restrict__ report) {
     __shared__ int ended;
     __shared__ double hs[kGmresM + 1], cr[kGmresM], sr[kGmresM];
     const int t = (int)threadIdx.x;
@@ -788,7 +789,12 @@ __global__ __launch_bounds__(256) void gm_finish(const double* __restrict__ part
     sc[S_RES] = res;
     const bool stop = res <= rtol || !isfinite(res) || hn == 0.0 || !(r > 0.0) || it >= max_iter;
     if (stop) fl[F_STOP] = 1;
-    if (stop || j + 1 == kGmresM) __hip_atomic_store(fl + F_CYC, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int32_t over = (stop || j + 1 == kGmresM) ? 1 : 0;
+    if (over) __hip_atomic_store(fl + F_CYC, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (report) {
+        __hip_atomic_store(&report->res, res, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&report->ended, over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // y = R^-1 g over the cycle's F_J steps (upper triangular H), one wave: column
@@ -1129,17 +1135,37 @@ int krylov_solve(const char* who, const fem_csr* csr, const void* K_vals, fem_pr
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             return e;
         };
-        auto read_flags = [&]() -> hipError_t {  // within a cycle: the flags only
-            hipError_t e = hipMemcpyAsync(flh, w.fl, sizeof(flh), hipMemcpyDeviceToHost, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);
-            return e;
-        };
         FEM_HIP_CHECK(read_back());
         const int per = gs_per(n), ngs = gs_blocks(n);
         const bool fuse = ngs <= kGsFuse;
         const unsigned nnb = std::min<unsigned>(kGrid, nbn);
+        // A multigrid step costs far more than waiting for it, so the host
+        // learns of every step's end and stops launching once the cycle is
+        // over; but it enqueues the next step before it waits for this one
+        // (the device idled 35 us per step otherwise: the copy, the
+        // synchronisation and the first launch after it), unless the
+        // residuals so far, extrapolated, say that this one converges.  A
+        // step enqueued in vain leaves at once, kernel by kernel (2 to 3 us
+        // each).
+        StepReport* reports = amg ? amg_reports(amg) : nullptr;
         while (!flh[F_STOP]) {
-            for (int j = 0; j < kGmresM; ++j) {
+            double r1 = res, r2 = 10.0 * res;  // the last two residuals known
+            bool over = false;
+            auto wait_for = [&](int j) -> hipError_t {
+                const hipError_t e = hipEventSynchronize(amg_report_event(amg, j & 1));
+                const volatile StepReport* q = reports + (j & 1);
+                over = q->ended != 0;
+                r2 = r1;
+                r1 = q->res;
+                return e;
+            };
+            for (int j = 0; j < kGmresM && !over; ++j) {
+                const bool ahead =
+                    j > 0 && flh[F_ITER] + j < max_iter && r1 * std::min(1.0, r1 / r2) > 1.5 * rtol;
+                if (amg && j > 0 && !ahead) {
+                    FEM_HIP_CHECK(wait_for(j - 1));
+                    if (over) break;
+                }
                 double* vj = g.V + (int64_t)j * g.ldv;
                 double* vn = g.V + (int64_t)(j + 1) * g.ldv;
                 double* zj = flex ? g.Z + (int64_t)j * g.ldv : w.ph;
@@ -1152,13 +1178,12 @@ int krylov_solve(const char* who, const fem_csr* csr, const void* K_vals, fem_pr
                 if (per == 1) gram_schmidt<1>(n, j, ngs, fuse, g, vn, w.part0, cyc, s);
                 else gram_schmidt<4>(n, j, ngs, fuse, g, vn, w.part0, cyc, s);
                 hipLaunchKernelGGL(gm_finish, dim3(1 + nnb), dim3(256), 0, s, w.part0, ngs, j, g.H, g.cs, g.sn, g.g,
-                                   w.sc, w.fl, rtol, max_iter, nn, vn, minv, amg ? mx : zn);
-                // a multigrid step costs far more than a stream synchronisation:
-                // stop launching once the cycle has ended
+                                   w.sc, w.fl, rtol, max_iter, nn, vn, minv, amg ? mx : zn,
+                                   amg ? reports + (j & 1) : nullptr);
                 if (amg) {
                     FEM_HIP_CHECK(hipGetLastError());
-                    FEM_HIP_CHECK(read_flags());
-                    if (flh[F_CYC]) break;
+                    FEM_HIP_CHECK(hipEventRecord(amg_report_event(amg, j & 1), s));
+                    if (ahead) FEM_HIP_CHECK(wait_for(j - 1));
                 }
             }
             // x += M (V y) (flexible: x += Z y); then the true residual of the restart
