@@ -126,3 +126,24 @@ def test_barlat_return_map_over_the_robustness_states(fem):
     assert list(g["diag"]) == [0, 0, 0, 0]
     assert hist_rel(g["hist"], o["hist"]) <= TOL_FP64
     assert rel_inf(g["R"], o["R"]) <= 1e-9
+
+
+@pytest.mark.parametrize("m", [2.0, 6.0, 7.5, 8.0])
+def test_exponents_match_oracle(fem, m):
+    """phi and its derivatives for m = 8 (three square roots), other integers
+    (powers by squaring) and a real exponent (pow), with points that stay
+    elastic, flow, and carry no stress at all."""
+    coef = np.array(synth.BARLAT_AA6111)
+    coef[18] = m
+    p = synth.with_model(synth.small_slab(104, 4, 3, 2, strain=0.004), 17, "voce", False, "per_element", barlat=coef)
+    still = p.conn[0]
+    p.d[still] = 0.0
+    p.hist_n[:, :8] = 0.0
+    say("barlat exponent", m)
+    o = oracle_forward(p)
+    assert (o["hist"][6] != p.hist_n[6]).any() and (o["hist"][6] == p.hist_n[6]).any()
+    g = gpu_forward(p, fem, fem.FP64)
+    assert rel_inf(g["R"], o["R"], residual_scale(p)) <= TOL_FP64
+    assert rel_inf(g["K"], o["K"]) <= TOL_FP64
+    assert hist_rel(g["hist"], o["hist"]) <= TOL_FP64
+    assert np.array_equal(g["diag"], o["diag"])
