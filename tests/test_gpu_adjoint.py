@@ -52,6 +52,54 @@ def test_transpose_matches_scipy(fem, prec_name):
     assert np.array_equal(B, ref)  # a permutation of the values: bit-exact
 
 
+@pytest.mark.parametrize("ranks", [True, False])
+@pytest.mark.parametrize("prec_name", ["FP64", "FP32_MIXED"])
+@pytest.mark.parametrize("fan", [5, 8, 12])
+def test_transpose_of_a_fan_is_exact(fem, fan, prec_name, ranks):
+    # wedges of hexahedra around a line: the two nodes on the line have `fan`
+    # incident elements and 4 fan + 2 neighbours (22, 34 and 50), more than one
+    # pass over 8 elements and over 64 rows of blocks; once with the slots of
+    # the pattern, once by the search that a pattern without them takes
+    ring = np.arange(fan)
+    layer = 1 + 2 * fan
+    conn = np.zeros((fan, 8), np.int32)
+    for z in (0, 1):
+        inner, outer = z * layer + 1 + 2 * ring, z * layer + 2 + 2 * ring
+        nxt = z * layer + 1 + 2 * ((ring + 1) % fan)
+        conn[:, 4 * z:4 * z + 4] = np.stack([np.full(fan, z * layer), inner, outer, nxt], 1)
+    th = 2 * np.pi * ring / fan
+    X = np.zeros((2 * (1 + 2 * fan), 3))
+    for z in (0, 1):
+        X[z * layer:(z + 1) * layer, 2] = z
+        X[z * layer + 1 + 2 * ring, 0], X[z * layer + 1 + 2 * ring, 1] = np.cos(th), np.sin(th)
+        mid = th + np.pi / fan
+        X[z * layer + 2 + 2 * ring, 0], X[z * layer + 2 + 2 * ring, 1] = 2 * np.cos(mid), 2 * np.sin(mid)
+    dev = torch.device("cuda:0")
+    mesh = fem.Mesh(X, conn)
+    csr = fem.csr_pattern(mesh)
+    n = csr.n_rows
+    real = torch.float64 if prec_name == "FP64" else torch.float32
+    rng = np.random.default_rng(85 + fan)
+    K = torch.as_tensor(rng.standard_normal(csr.nnz), device=dev).to(real)
+    bc = torch.as_tensor(rng.random(n) < 0.2, device=dev).to(torch.uint8)
+    bc[0] = 1  # a dof of a node on the line
+    if not ranks:
+        csr = fem.Csr(csr.row_ptr, csr.col_idx, None, csr.nnz, csr.n_rows, csr.node_elem_ptr, csr.node_elem)
+    say("transpose of a fan", fan, prec_name, ranks, csr.nnz)
+    KT = fem.csr_transpose(csr, K, bc_mask=bc)
+    torch.cuda.synchronize()
+    rp, ci = csr.row_ptr.cpu().numpy(), csr.col_idx.cpu().numpy()
+    rows = np.repeat(np.arange(n), np.diff(rp))
+    A, B = np.zeros((n, n)), np.zeros((n, n))
+    A[rows, ci] = K.double().cpu().numpy()
+    B[rows, ci] = KT.double().cpu().numpy()
+    ref = A.T.copy()
+    m = bc.bool().cpu().numpy()
+    ref[m] = 0.0
+    ref[m, np.nonzero(m)[0]] = 1.0
+    assert np.array_equal(B, ref)  # a permutation of the values
+
+
 MODELS = {"plain": ("swift", False, None), "voce_orient_pe": ("voce", False, "per_element"),
           "fbar": ("swift", True, None), "fbar_voce_orient": ("voce", True, "uniform")}
 
