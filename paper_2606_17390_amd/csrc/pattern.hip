@@ -3,14 +3,17 @@
 // the element matrices are later scattered straight into its value array).
 //
 // Steps, all on the device:
-//   1. node -> element incidence by counting and a prefix scan;
+//   1. node -> element incidence: an atomic counter per node gives each entry
+//      of conn its place among the node's entries, a scan the node's start;
 //   2. per node, the sorted unique list of nodes sharing an element (<= 64):
-//      one wave per node sorts the (element, node) candidates of up to 8
-//      incident elements across its lanes and keeps the first of equal ones;
+//      a wave sorts the 64 candidates of up to 8 incident elements across its
+//      lanes and keeps the first of equal ones;
 //   3. row_ptr from a scan of the neighbour counts (rows of one node have
 //      equal length 3*deg);
-//   4. col_idx rows and elem_rank (position of node J in node I's list),
-//      written by the same wave per node.
+//   4. col_idx rows, elem_rank (position of node J in node I's list) and the
+//      incidence in ascending order, written by the same wave.
+// The call that fills col_idx takes row_ptr from the caller and does step 1
+// and the sort of step 2 only.
 #include <hip/hip_runtime.h>
 
 #include "fem_internal.h"
@@ -23,29 +26,82 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanChunk = kScanThreads * kScanItems;
 
+constexpr int kCountPer = 4;  // conn entries per thread of the incidence kernels
+
 enum { ERR_RANGE = 1, ERR_ORPHAN = 2, ERR_DEGREE = 4 };
 
-__global__ void count_incidence(const int32_t* __restrict__ conn, int64_t n_entries, int32_t n_nodes,
-                                int32_t* __restrict__ cnt, int32_t* __restrict__ err) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_entries) return;
-    const int32_t n = conn[i];
-    if (n < 0 || n >= n_nodes) {
-        atomicOr(err, ERR_RANGE);
-        return;
+// Bound by the atomics, which are done at the memory side (3.9 M of them take
+// 87 us): a workgroup counts its 4096 entries in an LDS hash table first, and
+// adds once per distinct node (a third of the entries or fewer where elements
+// next to each other follow each other).  pos keeps an entry's place among its node's
+// entries, so that fill_incidence needs no atomics.  517,000 nodes, 3.9 M
+// entries: 87 us, and 128 us for an atomic fill; 55 us (69 us with 2048
+// entries, 88 us with 1024) and 26 us now.
+constexpr int kCountThreads = 1024;
+constexpr int kCountSlots = 8192;  // 2^13, at most half full
+
+__global__ __launch_bounds__(kCountThreads) void count_incidence(const int32_t* __restrict__ conn,
+                                                                 int64_t n_entries, int32_t n_nodes,
+                                                                 int32_t* __restrict__ cnt,
+                                                                 int32_t* __restrict__ pos,
+                                                                 int32_t* __restrict__ err) {
+    __shared__ int32_t skey[kCountSlots];
+    __shared__ int32_t scnt[kCountSlots];
+    const int64_t base = (int64_t)blockIdx.x * (kCountThreads * kCountPer) + threadIdx.x;
+    int32_t n[kCountPer], place[kCountPer];
+    int slot[kCountPer];
+#pragma unroll
+    for (int u = 0; u < kCountPer; ++u) {
+        const int64_t i = base + (int64_t)kCountThreads * u;
+        n[u] = i < n_entries ? conn[i] : -2;
     }
-    atomicAdd(&cnt[n], 1);
+    for (int t = (int)threadIdx.x; t < kCountSlots; t += kCountThreads) {
+        skey[t] = -1;
+        scnt[t] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kCountPer; ++u) {
+        place[u] = 0;
+        slot[u] = -1;
+        if (n[u] == -2 && base + (int64_t)kCountThreads * u >= n_entries) continue;
+        if (n[u] < 0 || n[u] >= n_nodes) {
+            atomicOr(err, ERR_RANGE);
+            continue;
+        }
+        int h = (int)(((uint32_t)n[u] * 2654435761u) >> 19);
+        while (true) {
+            const int32_t was = atomicCAS(&skey[h], -1, n[u]);
+            if (was == -1 || was == n[u]) break;
+            h = (h + 1) & (kCountSlots - 1);
+        }
+        slot[u] = h;
+        place[u] = atomicAdd(&scnt[h], 1);
+    }
+    __syncthreads();
+    for (int t = (int)threadIdx.x; t < kCountSlots; t += kCountThreads)
+        if (skey[t] >= 0) scnt[t] = atomicAdd(&cnt[skey[t]], scnt[t]);  // now the first place of this workgroup
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kCountPer; ++u)
+        if (slot[u] >= 0) pos[base + (int64_t)kCountThreads * u] = scnt[slot[u]] + place[u];
 }
 
-__global__ void fill_incidence(const int32_t* __restrict__ conn, int64_t n_entries, int32_t n_nodes,
-                               const int64_t* __restrict__ inc_ptr, int32_t* __restrict__ fillc,
-                               int32_t* __restrict__ inc) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_entries) return;
-    const int32_t n = conn[i];
-    if (n < 0 || n >= n_nodes) return;
-    const int32_t pos = atomicAdd(&fillc[n], 1);
-    inc[inc_ptr[n] + pos] = (int32_t)i;  // conn entry 8e + local index
+// Workgroups of an XCD take one contiguous eighth of conn: the entries of
+// elements next to each other, which share nodes, meet in one L2.
+__global__ __launch_bounds__(256) void fill_incidence(const int32_t* __restrict__ conn, int64_t n_entries,
+                                                      int64_t n_chunk, int32_t n_nodes,
+                                                      const int64_t* __restrict__ inc_ptr,
+                                                      const int32_t* __restrict__ pos, int32_t* __restrict__ inc) {
+    const int64_t base = ((int64_t)(blockIdx.x & 7) * n_chunk + (blockIdx.x >> 3)) * (256 * kCountPer) + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kCountPer; ++u) {
+        const int64_t i = base + 256 * u;
+        if (i >= n_entries) continue;
+        const int32_t n = conn[i];
+        if (n < 0 || n >= n_nodes) continue;
+        inc[inc_ptr[n] + pos[i]] = (int32_t)i;  // conn entry 8e + local index
+    }
 }
 
 // Sorted unique neighbour list of node n (n included).  Returns the count or
@@ -70,10 +126,11 @@ __device__ int node_neighbours(int32_t n, const int32_t* __restrict__ conn, cons
     return cnt;
 }
 
-// ---- one wave per node (nodes with at most 8 incident elements; a node with
-// more takes the serial node_neighbours in lane 0)
+// ---- kNodes nodes per wave, one after the other (a node with more than 8
+// incident elements takes the serial node_neighbours in lane 0)
 
-constexpr int kPatWaves = 4;  // nodes (waves) per workgroup
+constexpr int kPatWaves = 4;  // waves per workgroup
+constexpr int kNodes = 8;     // nodes per wave
 
 __device__ inline void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -81,136 +138,217 @@ __device__ inline void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Ascending bitonic sort of one 64-bit key per lane across the wave.
-__device__ inline uint64_t wave_sort64(uint64_t key, int lane) {
-#pragma unroll
-    for (int k = 2; k <= 64; k <<= 1)
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const uint64_t other = __shfl_xor(key, j, 64);
-            const bool keep_min = (((lane & j) == 0) == ((lane & k) == 0));
-            key = keep_min ? (other < key ? other : key) : (other > key ? other : key);
-        }
-    return key;
+template <int CTRL>
+__device__ inline uint32_t dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);
 }
-
-// Lane (k, j) proposes node j of incident element k (k < 8); after the sort,
-// the sorted position p knows whether it starts a new value and that value's
-// index among the unique ones.  Returns the number of unique neighbours.
-struct WaveNbr {
-    int deg;
-    bool first;     // sorted position p holds the first copy of its value
-    int32_t value;  // value at sorted position p
-    int uidx;       // its index among the unique values
-    int origin;     // lane whose candidate sits at position p (-1: none)
-};
-__device__ inline WaveNbr wave_neighbours(uint64_t key, int lane) {
-    key = wave_sort64(key, lane);
-    const bool valid = key != ~0ull;
-    const uint64_t prev = __shfl_up(key, 1, 64);
-    const bool first = valid && (lane == 0 || (prev >> 32) != (key >> 32));
-    const uint64_t mask = __ballot(first);
-    const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-    WaveNbr r;
-    r.deg = __popcll(mask);
-    r.first = first;
-    r.value = (int32_t)(key >> 32);
-    r.uidx = __popcll(mask & upto) - 1;
-    r.origin = valid ? (int)(key & 63) : -1;
-    return r;
+// the value of lane ^ M
+template <int M>
+__device__ inline uint32_t lane_xor(uint32_t x, int lane) {
+    if constexpr (M == 1) return dpp<0xB1>(x);        // quad_perm 1 0 3 2
+    else if constexpr (M == 2) return dpp<0x4E>(x);   // quad_perm 2 3 0 1
+    else if constexpr (M == 3) return dpp<0x1B>(x);   // quad_perm 3 2 1 0
+    else if constexpr (M == 7) return dpp<0x141>(x);  // row_half_mirror
+    else if constexpr (M == 15) return dpp<0x140>(x); // row_mirror
+    else if constexpr (M == 8) return dpp<0x128>(x);  // row_ror:8
+    else if constexpr (M < 7) return dpp<0x141>(lane_xor<7 ^ M>(x, lane));
+    else if constexpr (M < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (M << 10) | 0x1f);
+    else return (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ M) << 2, (int)x);
 }
-
-__global__ __launch_bounds__(64 * kPatWaves) void node_degree_w(int32_t n_nodes, const int32_t* __restrict__ conn,
-                                                                 const int64_t* __restrict__ inc_ptr,
-                                                                 const int32_t* __restrict__ inc,
-                                                                 int32_t* __restrict__ deg, int32_t* __restrict__ err) {
-    const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-    const int64_t n = (int64_t)blockIdx.x * kPatWaves + w;
-    if (n >= n_nodes) return;
-    const int64_t k0 = inc_ptr[n], cnt = inc_ptr[n + 1] - k0;
-    int c;
-    if (cnt <= 8) {
-        const int kk = lane >> 3, j = lane & 7;
-        uint64_t key = ~0ull;
-        if (kk < cnt) key = ((uint64_t)(uint32_t)conn[(int64_t)(inc[k0 + kk] >> 3) * 8 + j] << 32) | (uint64_t)lane;
-        c = wave_neighbours(key, lane).deg;
+// min where bound is 0, max where it is ~0: the median of the three
+__device__ inline uint32_t min_or_max(uint32_t x, uint32_t y, uint32_t bound) {
+    const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
+    const uint32_t m = hi < bound ? hi : bound;
+    return lo > m ? lo : m;
+}
+template <int J>
+__device__ inline uint32_t merge_down(uint32_t x, const uint32_t (&bound)[6], int lane) {
+    if constexpr (J > 0) {
+        x = min_or_max(x, lane_xor<J>(x, lane), bound[__builtin_ctz(J)]);
+        return merge_down<J / 2>(x, bound, lane);
     } else {
-        int32_t nb[kMaxNbr];
-        c = (lane == 0) ? node_neighbours((int32_t)n, conn, inc_ptr, inc, nb) : 0;
+        return x;
     }
-    if (lane == 0) {
-        if (c < 0) {
-            atomicOr(err, ERR_DEGREE);
-            c = 0;
-        } else if (c == 0) {
-            atomicOr(err, ERR_ORPHAN);
-        }
-        deg[n] = c;
+}
+template <int K>
+__device__ inline uint32_t merge_up(uint32_t x, const uint32_t (&bound)[6], int lane) {
+    if constexpr (K <= 64) {
+        x = min_or_max(x, lane_xor<K - 1>(x, lane), bound[__builtin_ctz(K) - 1]);
+        return merge_up<2 * K>(merge_down<K / 4>(x, bound, lane), bound, lane);
+    } else {
+        return x;
     }
 }
 
-// Column indices of node n's three rows and the elem_rank entries of every
-// (element, local index) pair that is node n.
-__global__ __launch_bounds__(64 * kPatWaves) void node_fill_w(int32_t n_nodes, const int32_t* __restrict__ conn,
-                                                               const int64_t* __restrict__ inc_ptr,
-                                                               const int32_t* __restrict__ inc,
-                                                               const int32_t* __restrict__ row_ptr,
-                                                               int32_t* __restrict__ col_idx,
-                                                               uint8_t* __restrict__ rank) {
+// FILL false: neighbour counts of kNodes nodes.  FILL true: column indices of
+// the nodes' rows, the elem_rank entries of every (element, local index) pair
+// that is one of the nodes, and (out != NULL) their incidence in ascending
+// order.
+//
+// Bound by vector instructions: the bitonic sort of one 32-bit node number per
+// lane takes 21 exchanges of two instructions each (a DPP move and a median of
+// three; mirrored first steps, so that all merges ascend and 18 of the 21
+// partners are DPP patterns).  A lane finds its candidate's place by a binary
+// search of the sorted list in LDS.  The loads of the kNodes nodes are in
+// flight together, three dependent loads per wave and not per node, and an
+// XCD's workgroups take one contiguous eighth of the nodes, whose conn rows and
+// elem_rank lines then stay in one L2.  517,000 nodes: counts 250 us and fill
+// 307 us + 51 us (incidence by a thread per node) with a sort of 64-bit
+// (node, lane) pairs by LDS permutes, one node per wave; 55 us and 179 us now
+// (0.50 GB written; 88 us without the columns, 140 us without elem_rank).
+template <bool FILL>
+__global__ __launch_bounds__(64 * kPatWaves) void node_pass(
+    int32_t n_nodes, int64_t n_chunk, const int32_t* __restrict__ conn, const int64_t* __restrict__ inc_ptr,
+    const int32_t* __restrict__ inc, int32_t* __restrict__ deg_out, int32_t* __restrict__ err,
+    const int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx, uint8_t* __restrict__ rank,
+    int32_t* __restrict__ out_ptr, int32_t* __restrict__ out) {
     __shared__ int32_t snb[kPatWaves][kMaxNbr];
-    __shared__ int32_t srk[kPatWaves][64];
-    __shared__ int32_t sdeg[kPatWaves];
+    __shared__ int32_t scol[kPatWaves][3 * kMaxNbr];
+    __shared__ uint32_t scand[kPatWaves][kNodes * 64];
     const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-    const int64_t n = (int64_t)blockIdx.x * kPatWaves + w;
-    if (n >= n_nodes) return;
-    const int64_t k0 = inc_ptr[n], k1 = inc_ptr[n + 1], cnt = k1 - k0;
-    const int kk = lane >> 3, j = lane & 7;
-    int deg;
-    if (cnt <= 8) {
-        int32_t entry = -1;
-        uint64_t key = ~0ull;
-        if (kk < cnt) {
-            entry = inc[k0 + kk];
-            key = ((uint64_t)(uint32_t)conn[(int64_t)(entry >> 3) * 8 + j] << 32) | (uint64_t)lane;
+    const int64_t n0 =
+        (((int64_t)(blockIdx.x & 7) * n_chunk + (blockIdx.x >> 3)) * kPatWaves + w) * kNodes;
+    if (n0 >= n_nodes) return;  // the whole wave; no workgroup barrier below
+    // lane (m, q): the q-th incident entry of node n0 + m
+    const int m = lane >> 3, q = lane & 7;
+    int64_t k0 = 0;
+    int32_t cnt = 0, row0 = 0, entry = INT32_MAX;
+    if (n0 + m < n_nodes) {
+        k0 = inc_ptr[n0 + m];
+        cnt = (int32_t)(inc_ptr[n0 + m + 1] - k0);
+        if constexpr (FILL) row0 = row_ptr[3 * (n0 + m)];
+    }
+    if (q < cnt) entry = inc[k0 + q];
+    const int nn = (int)(n_nodes - n0 < kNodes ? n_nodes - n0 : kNodes);
+
+    // lane (q, j) = (m, q): node j of the q-th incident element, for each node
+    uint32_t cand[kNodes];
+#pragma unroll
+    for (int t = 0; t < kNodes; ++t) {
+        const int32_t e = __builtin_amdgcn_ds_bpermute((8 * t + m) << 2, entry);
+        cand[t] = ~0u;
+        if (e != INT32_MAX) cand[t] = (uint32_t)conn[(int64_t)(e & ~7) + q];
+    }
+#pragma unroll
+    for (int t = 0; t < kNodes; ++t) scand[w][64 * t + lane] = cand[t];
+    uint32_t bound[6];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) bound[t] = (lane >> t) & 1 ? ~0u : 0u;
+
+    if constexpr (FILL) {
+        if (out) {
+            if (n0 + m < n_nodes && q == 0) out_ptr[n0 + m] = (int32_t)k0;
+            if (n0 + nn == n_nodes && lane == 0) out_ptr[n_nodes] = (int32_t)inc_ptr[n_nodes];
+            const uint32_t x = (uint32_t)entry;
+            const int place = (lane_xor<1>(x, lane) < x) + (lane_xor<2>(x, lane) < x) + (lane_xor<3>(x, lane) < x) +
+                              (lane_xor<4>(x, lane) < x) + (lane_xor<5>(x, lane) < x) + (lane_xor<6>(x, lane) < x) +
+                              (lane_xor<7>(x, lane) < x);
+            if (cnt <= 8) {
+                if (q < cnt) out[k0 + place] = entry;
+            } else if (q == 0) {
+                for (int64_t k = k0; k < k0 + cnt; ++k) {
+                    const int32_t v = inc[k];
+                    int64_t p = k;
+                    while (p > k0 && out[p - 1] > v) {
+                        out[p] = out[p - 1];
+                        --p;
+                    }
+                    out[p] = v;
+                }
+            }
         }
-        const WaveNbr r = wave_neighbours(key, lane);
-        deg = r.deg;
-        if (r.first) snb[w][r.uidx] = r.value;
-        if (r.origin >= 0) srk[w][r.origin] = r.uidx;
-        wave_sync_lds();
-        if (entry >= 0) rank[(int64_t)entry * 8 + j] = (uint8_t)srk[w][lane];
-    } else {
-        if (lane == 0) {
-            int32_t nb[kMaxNbr];
-            const int c = node_neighbours((int32_t)n, conn, inc_ptr, inc, nb);
-            for (int t = 0; t < c; ++t) snb[w][t] = nb[t];
-            sdeg[w] = c;
+    }
+
+    // the three rows of node n0 + t: 9 deg columns in a row
+    auto write_columns = [&](int t, int deg) {
+        int32_t* row = col_idx + __builtin_amdgcn_readlane(row0, 8 * t);
+        const int len = 3 * deg;
+        for (int b = 0; b < 3 * len; b += 256) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int u = b + 64 * k + lane;
+                if (u < 3 * len) row[u] = scol[w][u - (u >= len ? len : 0) - (u >= 2 * len ? len : 0)];
+            }
         }
         wave_sync_lds();
-        deg = sdeg[w];
-        if (deg <= 0) return;  // reported by the counting call
-        for (int64_t c = k0; c < k1; c += 8) {
-            if (c + kk < k1) {
-                const int32_t entry = inc[c + kk];
-                const int32_t v = conn[(int64_t)(entry >> 3) * 8 + j];
+    };
+
+    int32_t my_deg = 0;  // lane t: of node n0 + t
+    uint32_t more = 0;   // the nodes with more than 8 elements
+    // no load in this loop: one would make the wave wait for the stores of the node before
+#pragma unroll 1
+    for (int t = 0; t < nn; ++t) {
+        if (__builtin_amdgcn_readlane(cnt, 8 * t) > 8) {
+            more |= 1u << t;
+            continue;
+        }
+        const uint32_t own = scand[w][64 * t + lane];
+        const uint32_t x = merge_up<2>(own, bound, lane);
+        const uint32_t prev = dpp<0x138>(x);  // wave_shr:1
+        const bool first = x != ~0u && (lane == 0 || prev != x);
+        const uint64_t mask = __ballot(first);
+        const int deg = __popcll(mask);
+        if (lane == t) my_deg = deg;
+        if constexpr (FILL) {
+            const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (lane >= deg) snb[w][lane] = INT32_MAX;
+            if (first) {
+                snb[w][below] = (int32_t)x;
+#pragma unroll
+                for (int b = 0; b < 3; ++b) scol[w][3 * below + b] = 3 * (int32_t)x + b;
+            }
+            wave_sync_lds();
+            const int32_t e = __builtin_amdgcn_ds_bpermute((8 * t + m) << 2, entry);
+            if (e != INT32_MAX) {
+                const int32_t v = (int32_t)own;
+                int p = 0;
+#pragma unroll
+                for (int step = 32; step > 0; step >>= 1)
+                    if (snb[w][p + step - 1] < v) p += step;
+                rank[(int64_t)e * 8 + q] = (uint8_t)p;
+            }
+            write_columns(t, deg);
+        }
+    }
+    while (more) {
+        const int t = __builtin_ctz(more);
+        more &= more - 1;
+        const int64_t k0t = inc_ptr[n0 + t], k1t = inc_ptr[n0 + t + 1];
+        int s = 0;
+        if (lane == 0) s = node_neighbours((int32_t)(n0 + t), conn, inc_ptr, inc, snb[w]);
+        wave_sync_lds();
+        const int deg = __builtin_amdgcn_readfirstlane(s);
+        if (lane == t) my_deg = deg;
+        if constexpr (FILL) {
+            if (deg <= 0) continue;  // reported by the counting call
+            if (lane < deg)
+                for (int b = 0; b < 3; ++b) scol[w][3 * lane + b] = 3 * snb[w][lane] + b;
+            wave_sync_lds();
+            for (int64_t k = k0t + m; k < k1t; k += 8) {
+                const int32_t e = inc[k];
+                const int32_t v = conn[(int64_t)(e & ~7) + q];
                 int lo = 0, hi = deg - 1;
                 while (lo < hi) {
                     const int mid = (lo + hi) >> 1;
                     if (snb[w][mid] < v) lo = mid + 1;
                     else hi = mid;
                 }
-                rank[(int64_t)entry * 8 + j] = (uint8_t)lo;
+                rank[(int64_t)e * 8 + q] = (uint8_t)lo;
             }
+            write_columns(t, deg);
         }
     }
-    int32_t* row = col_idx + row_ptr[3 * n];
-    const int32_t len = 3 * deg;
-    for (int u = lane; u < deg; u += 64) {
-        const int32_t v = snb[w][u];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) row[a * len + 3 * u + b] = 3 * v + b;
+    if constexpr (!FILL) {
+        if (lane < nn) {
+            if (my_deg < 0) {
+                atomicOr(err, ERR_DEGREE);
+                my_deg = 0;
+            } else if (my_deg == 0) {
+                atomicOr(err, ERR_ORPHAN);
+            }
+            deg_out[n0 + lane] = my_deg;
+        }
     }
 }
 
@@ -232,7 +370,8 @@ __global__ void node_columns(int32_t n_nodes, const int32_t* __restrict__ conn, 
     }
 }
 
-// node -> conn-entry incidence in ascending order (deterministic assembly)
+// node -> conn-entry incidence in ascending order (deterministic assembly),
+// for a caller that asks for no elem_rank
 __global__ void write_incidence(int32_t n_nodes, const int64_t* __restrict__ inc_ptr,
                                 const int32_t* __restrict__ inc, int32_t* __restrict__ out_ptr,
                                 int32_t* __restrict__ out) {
@@ -252,12 +391,14 @@ __global__ void write_incidence(int32_t n_nodes, const int64_t* __restrict__ inc
     }
 }
 
-__global__ void write_row_ptr(int32_t n_nodes, const int32_t* __restrict__ deg, const int64_t* __restrict__ dscan,
-                              int32_t* __restrict__ row_ptr) {
+// also puts the error flags beside the total, for one read of both
+__global__ void write_row_ptr(int32_t n_nodes, const int32_t* __restrict__ deg, int64_t* __restrict__ dscan,
+                              const int32_t* __restrict__ err, int32_t* __restrict__ row_ptr) {
     int32_t n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n > n_nodes) return;
     if (n == n_nodes) {
         row_ptr[3 * (int64_t)n_nodes] = (int32_t)(9 * dscan[n_nodes]);
+        dscan[n_nodes + 1] = *err;
         return;
     }
     const int64_t base = 9 * dscan[n];
@@ -348,14 +489,14 @@ hipError_t exclusive_scan(const int32_t* in, int64_t n, int64_t* out, int64_t* b
 }
 
 struct PatternWs {
-    int32_t* cnt;      // [n_nodes]
+    int32_t* cnt;      // [n_nodes + 1], the last one the error flags
     int64_t* inc_ptr;  // [n_nodes + 1]
-    int32_t* fillc;    // [n_nodes]
+    int32_t* pos;      // [8 n_elems] place of a conn entry among its node's
     int32_t* inc;      // [8 n_elems]
     int32_t* deg;      // [n_nodes]
-    int64_t* dscan;    // [n_nodes + 1]
+    int64_t* dscan;    // [n_nodes + 2], the last one the error flags
     int64_t* bsum;     // scan block sums
-    int32_t* err;      // [1]
+    int32_t* err;      // = cnt + n_nodes
 };
 
 template <typename C>
@@ -363,13 +504,12 @@ void carve_pattern(C& c, int32_t n_nodes, int32_t n_elems, PatternWs* w) {
     const size_t nb = ((size_t)n_nodes + kScanChunk) / kScanChunk + 1;
     auto cnt = c.template take<int32_t>((size_t)n_nodes + 1);
     auto ip = c.template take<int64_t>((size_t)n_nodes + 1);
-    auto fc = c.template take<int32_t>((size_t)n_nodes + 1);
+    auto pos = c.template take<int32_t>((size_t)n_elems * 8 + 1);
     auto inc = c.template take<int32_t>((size_t)n_elems * 8 + 1);
     auto deg = c.template take<int32_t>((size_t)n_nodes + 1);
-    auto ds = c.template take<int64_t>((size_t)n_nodes + 1);
+    auto ds = c.template take<int64_t>((size_t)n_nodes + 2);
     auto bs = c.template take<int64_t>(nb);
-    auto er = c.template take<int32_t>(64);
-    if (w) *w = PatternWs{cnt, ip, fc, inc, deg, ds, bs, er};
+    if (w) *w = PatternWs{cnt, ip, pos, inc, deg, ds, bs, cnt + n_nodes};
 }
 
 // take<> of the counter returns void; adapt so the same carving code runs
@@ -382,27 +522,27 @@ struct CountAdapter {
     }
 };
 
-// Steps 1-2 (+ degree scan): incidence, neighbour counts, row_ptr.
+// Step 1.
 int build_incidence(const fem_mesh* m, const PatternWs& w, hipStream_t s) {
     const int64_t ne8 = (int64_t)m->n_elems * 8;
     const int32_t nn = m->n_nodes;
     FEM_HIP_CHECK(zero_bytes(w.cnt, sizeof(int32_t) * ((size_t)nn + 1), s));
-    FEM_HIP_CHECK(zero_bytes(w.fillc, sizeof(int32_t) * ((size_t)nn + 1), s));
-    FEM_HIP_CHECK(zero_bytes(w.err, sizeof(int32_t), s));
-    const int T = 256;
+    const int64_t per = kCountThreads * kCountPer, n_chunk = ((ne8 + 256 * kCountPer - 1) / (256 * kCountPer) + 7) / 8;
     if (ne8 > 0)
-        hipLaunchKernelGGL(count_incidence, dim3((unsigned)((ne8 + T - 1) / T)), dim3(T), 0, s, m->conn, ne8, nn,
-                           w.cnt, w.err);
+        hipLaunchKernelGGL(count_incidence, dim3((unsigned)((ne8 + per - 1) / per)), dim3(kCountThreads), 0, s,
+                           m->conn, ne8, nn, w.cnt, w.pos, w.err);
     FEM_HIP_CHECK(exclusive_scan(w.cnt, nn, w.inc_ptr, w.bsum, s));
     if (ne8 > 0)
-        hipLaunchKernelGGL(fill_incidence, dim3((unsigned)((ne8 + T - 1) / T)), dim3(T), 0, s, m->conn, ne8, nn,
-                           w.inc_ptr, w.fillc, w.inc);
-    if (nn > 0)
-        hipLaunchKernelGGL(node_degree_w, dim3((unsigned)((nn + kPatWaves - 1) / kPatWaves)), dim3(64 * kPatWaves), 0,
-                           s, nn, m->conn, w.inc_ptr, w.inc, w.deg, w.err);
-    FEM_HIP_CHECK(exclusive_scan(w.deg, nn, w.dscan, w.bsum, s));
+        hipLaunchKernelGGL(fill_incidence, dim3((unsigned)(8 * n_chunk)), dim3(256), 0, s, m->conn, ne8, n_chunk, nn,
+                           w.inc_ptr, w.pos, w.inc);
     FEM_HIP_CHECK(hipGetLastError());
     return FEM_OK;
+}
+
+// Workgroups of node_pass: 8 contiguous ranges of n_chunk workgroups.
+int64_t node_chunk(int32_t n_nodes) {
+    const int64_t per = kPatWaves * kNodes;
+    return ((n_nodes + per - 1) / per + 7) / 8;
 }
 
 }  // namespace
@@ -438,15 +578,21 @@ extern "C" int fem_csr_pattern(const fem_mesh* mesh, fem_csr* csr, void* ws, siz
     if (rc) return rc;
     const int T = 256;
     const int32_t nn = mesh->n_nodes;
+    const int64_t n_chunk = node_chunk(nn);
+    const dim3 grid((unsigned)(8 * n_chunk)), block(64 * kPatWaves);
     if (!csr->col_idx) {
+        if (nn > 0)
+            hipLaunchKernelGGL((node_pass<false>), grid, block, 0, s, nn, n_chunk, mesh->conn, w.inc_ptr, w.inc,
+                               w.deg, w.err, (const int32_t*)nullptr, (int32_t*)nullptr, (uint8_t*)nullptr,
+                               (int32_t*)nullptr, (int32_t*)nullptr);
+        FEM_HIP_CHECK(exclusive_scan(w.deg, nn, w.dscan, w.bsum, s));
         hipLaunchKernelGGL(write_row_ptr, dim3((unsigned)((nn + 1 + T - 1) / T)), dim3(T), 0, s, nn, w.deg, w.dscan,
-                           csr->row_ptr);
+                           w.err, csr->row_ptr);
         FEM_HIP_CHECK(hipGetLastError());
-        int64_t total = 0;
-        int32_t err = 0;
-        FEM_HIP_CHECK(hipMemcpyAsync(&total, w.dscan + nn, sizeof total, hipMemcpyDeviceToHost, s));
-        FEM_HIP_CHECK(hipMemcpyAsync(&err, w.err, sizeof err, hipMemcpyDeviceToHost, s));
+        int64_t report[2] = {0, 0};
+        FEM_HIP_CHECK(hipMemcpyAsync(report, w.dscan + nn, sizeof report, hipMemcpyDeviceToHost, s));
         FEM_HIP_CHECK(hipStreamSynchronize(s));
+        const int64_t total = report[0], err = report[1];
         if (err & ERR_RANGE) return set_error(FEM_EMESH, "fem_csr_pattern: node index out of range in conn");
         if (err & ERR_DEGREE) return set_error(FEM_EMESH, "fem_csr_pattern: a node has more than 64 neighbours");
         if (err & ERR_ORPHAN) return set_error(FEM_EMESH, "fem_csr_pattern: a node belongs to no element");
@@ -455,17 +601,19 @@ extern "C" int fem_csr_pattern(const fem_mesh* mesh, fem_csr* csr, void* ws, siz
         csr->nnz = 9 * total;
         return FEM_OK;
     }
-    if (nn > 0) {
-        if (csr->elem_rank)
-            hipLaunchKernelGGL(node_fill_w, dim3((unsigned)((nn + kPatWaves - 1) / kPatWaves)), dim3(64 * kPatWaves),
-                               0, s, nn, mesh->conn, w.inc_ptr, w.inc, csr->row_ptr, csr->col_idx, csr->elem_rank);
-        else
+    const bool inc_out = csr->node_elem_ptr && csr->node_elem;
+    if (csr->elem_rank && nn > 0) {
+        hipLaunchKernelGGL((node_pass<true>), grid, block, 0, s, nn, n_chunk, mesh->conn, w.inc_ptr, w.inc,
+                           (int32_t*)nullptr, (int32_t*)nullptr, csr->row_ptr, csr->col_idx, csr->elem_rank,
+                           inc_out ? csr->node_elem_ptr : nullptr, inc_out ? csr->node_elem : nullptr);
+    } else {
+        if (nn > 0)
             hipLaunchKernelGGL(node_columns, dim3((unsigned)((nn + T - 1) / T)), dim3(T), 0, s, nn, mesh->conn,
                                w.inc_ptr, w.inc, csr->row_ptr, csr->col_idx);
+        if (inc_out)
+            hipLaunchKernelGGL(write_incidence, dim3((unsigned)((nn + 1 + T - 1) / T)), dim3(T), 0, s, nn, w.inc_ptr,
+                               w.inc, csr->node_elem_ptr, csr->node_elem);
     }
-    if (csr->node_elem_ptr && csr->node_elem)
-        hipLaunchKernelGGL(write_incidence, dim3((unsigned)((nn + 1 + T - 1) / T)), dim3(T), 0, s, nn, w.inc_ptr,
-                           w.inc, csr->node_elem_ptr, csr->node_elem);
     FEM_HIP_CHECK(hipGetLastError());
     return FEM_OK;
 }

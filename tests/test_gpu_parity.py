@@ -87,6 +87,33 @@ def test_pattern_incidence_and_rebuild_in_place(fem):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("fan,copies", [(3, 1), (8, 3), (9, 2), (15, 5), (8, 140)])
+def test_pattern_of_fans_bit_exact(fem, fan, copies):
+    """Separate fans of wedge-shaped hexahedra around a line, their nodes and
+    elements in random order: nodes with 2 and with `fan` incident elements
+    (fewer than, exactly and more than eight) and 4 fan + 2 neighbours (up to
+    62), node counts that fill no wave or workgroup, entries of one node far
+    apart in conn (the last case spans three workgroups of the count)."""
+    rng = np.random.default_rng(44 + fan + copies)
+    ring, layer = np.arange(fan), 1 + 2 * fan
+    one = np.zeros((fan, 8), np.int64)
+    for z in (0, 1):
+        one[:, 4 * z:4 * z + 4] = z * layer + np.stack(
+            [np.zeros(fan, int), 1 + 2 * ring, 2 + 2 * ring, 1 + 2 * ((ring + 1) % fan)], 1)
+    n = 2 * layer * copies
+    conn = (one[None] + 2 * layer * np.arange(copies)[:, None, None]).reshape(-1, 8)
+    conn = rng.permutation(n)[rng.permutation(conn)].astype(np.int32)
+    say("pattern of fans", fan, copies, n, len(conn))
+    csr = fem.csr_pattern(fem.Mesh(np.zeros((n, 3)), conn))
+    rp, ci, rank = oracle.csr_pattern(conn, n)
+    flat = conn.ravel().astype(np.int64)
+    assert np.array_equal(csr.row_ptr.cpu().numpy(), rp)
+    assert np.array_equal(csr.col_idx.cpu().numpy(), ci)
+    assert np.array_equal(csr.elem_rank.cpu().numpy(), rank)
+    assert np.array_equal(csr.node_elem.cpu().numpy(), np.argsort(flat, kind="stable"))
+    assert np.array_equal(csr.node_elem_ptr.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(flat))]))
+
+
 def test_pattern_rejects_bad_meshes(fem):
     X, conn = synth.hex_grid(2, 1, 1)
     mesh = fem.Mesh(np.vstack([X, [[9.0, 9.0, 9.0]]]), conn)  # orphan node
