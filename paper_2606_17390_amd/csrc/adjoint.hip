@@ -108,15 +108,24 @@ __device__ inline void reverse_plastic(const Modes& md, const Local& loc, double
     }
 }
 
+// Bound by FP64 vector instructions, of which one wave issues at most one every
+// 8 cycles: two waves per SIMD share one that takes 4.  For them a workgroup may
+// hold 20 KB of LDS and a lane 256 registers, so the sums over an element's
+// Gauss points reuse the space of the nodes, eight rows at a time, and that of
+// the gradients they are formed from.  Oriented F-bar, 202,000 elements: 320 us
+// with one wave per SIMD (31 KB of LDS, 268 registers), 250 us now (8 to 20
+// registers spilled).
 template <int VAR>
-__global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
+__global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(2))) void hadj_kernel(const AdjArgs a) {
     constexpr bool ORIENT = (VAR & kVarOrientA) != 0;
     constexpr bool FBAR = (VAR & kVarFbarA) != 0;
     constexpr int EPB = kAdjEpb;
     __shared__ double sN[EPB][8][9];   // X, d, lambda of the element's nodes
     __shared__ double sG[EPB][8][25];  // g^ = Q^T grad N per Gauss point (odd row length: no bank conflicts)
-    __shared__ double red[24][kAdjBlock + 1];
     __shared__ double sQb[FBAR ? EPB : 1][24];
+    // element sums over the Gauss points: eight rows at a time, in the space of sN
+    static_assert(8 * (kAdjBlock + 1) <= EPB * 8 * 9, "the rows of a sum fit in sN");
+    double (*red)[kAdjBlock + 1] = reinterpret_cast<double (*)[kAdjBlock + 1]>(&sN[0][0][0]);
     const int tid = threadIdx.x, slot = tid >> 3, gp = tid & 7;
     const int64_t e_raw = (int64_t)blockIdx.x * EPB + slot;
     const bool valid = e_raw < a.n_elems;
@@ -302,7 +311,8 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
         for (int k = 0; k < 6; ++k) a.hbar[k * a.n_gp + q] = mu[k] - mw<double>(k) * v[k];
         a.hbar[6 * a.n_gp + q] = hb_a;
     }
-    // thetabar summed over the element's Gauss points
+    // thetabar summed over the element's Gauss points (sN is read no more)
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < 7; ++k) red[k][tid] = th_bar[k];
     __syncthreads();
@@ -342,28 +352,26 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
             for (int p = 0; p < 3; ++p) sg += Xh[i][p] * fh[i][p];
         sg *= 1.0 / 3.0;
 #pragma unroll
-        for (int J = 0; J < 8; ++J)
+        for (int b = 0; b < 3; ++b) {
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
+            for (int J = 0; J < 8; ++J) {
                 double x = 0.0;
 #pragma unroll
                 for (int s2 = 0; s2 < 3; ++s2) x += sG[slot][gp][3 * J + s2] * fc[b][s2];
-                red[3 * J + b][tid] = cw * beta * x;
+                red[J][tid] = cw * beta * x;
             }
-        __syncthreads();
-        if (gp < 8) {
+            __syncthreads();
+            double s = 0.0;
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                double s = 0.0;
-#pragma unroll
-                for (int g2 = 0; g2 < 8; ++g2) s += red[3 * gp + b][slot * 8 + g2];
-                sQb[slot][3 * gp + b] = s;
-            }
+            for (int g2 = 0; g2 < 8; ++g2) s += red[gp][slot * 8 + g2];
+            sQb[slot][3 * gp + b] = s;
+            __syncthreads();
         }
-        __syncthreads();
     }
+    // the values of (J, b) take the place of the g^ they are formed from
 #pragma unroll
-    for (int J = 0; J < 8; ++J)
+    for (int J = 0; J < 8; ++J) {
+        double y[3];
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             double x = Xh[b][0] * sG[slot][gp][3 * J] + Xh[b][1] * sG[slot][gp][3 * J + 1] +
@@ -374,8 +382,11 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
                 for (int s2 = 0; s2 < 3; ++s2) qg += sG[slot][gp][3 * J + s2] * fc[b][s2];
                 x = beta * x - sg * beta * qg;
             }
-            red[3 * J + b][tid] = x;
+            y[b] = x;
         }
+#pragma unroll
+        for (int b = 0; b < 3; ++b) sG[slot][gp][3 * J + b] = y[b];
+    }
     __syncthreads();
     const double S = FBAR ? sum8(sg) : 0.0;
     if (valid) {
@@ -383,7 +394,7 @@ __global__ __launch_bounds__(kAdjBlock) void hadj_kernel(const AdjArgs a) {
         for (int b = 0; b < 3; ++b) {
             double s = 0.0;
 #pragma unroll
-            for (int g2 = 0; g2 < 8; ++g2) s += red[3 * gp + b][slot * 8 + g2];
+            for (int g2 = 0; g2 < 8; ++g2) s += sG[slot][g2][3 * gp + b];
             if constexpr (FBAR) s += S * sQb[slot][3 * gp + b];
             a.ue[e * 24 + 3 * gp + b] = s;
         }
