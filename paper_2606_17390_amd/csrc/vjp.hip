@@ -125,10 +125,17 @@ __device__ inline void kin_log_v(const double (*nd)[9], int gp, GPv<R>& s, doubl
     }
 }
 
-// The FP32 form is held to two waves per SIMD (a few registers spill; measured
-// faster than one wave per SIMD without spills).
+// Bound by FP64 vector instructions (the local update and its adjoint run in
+// FP64 in both precisions).  One wave issues at most one every 8 cycles, two
+// waves per SIMD share one that takes 4 (the FP64 form ran at 57 % of the vector
+// rate with one wave), so a lane is held to 256 registers.  What fits it in
+// them: the cotangent of the stress is six numbers formed from the kinematics
+// before the local update, so no gradient, H or Q has to be kept across it, and
+// the constants of the element loop are not hoisted out of it (build flag).
+// 60,000 elements, FP64: 80 us with one wave and 23 KB of parked values per
+// wave, 70 us now; 1.2 M elements, mixed: 1190 us to 1110 us.
 template <typename R, int BLOCK, bool FIXUP, int VAR>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(std::is_same<R, float>::value && !FIXUP ? 2 : 1)))
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
 void vjp_kernel(const VjpArgs a) {
     constexpr int EPB = BLOCK / 8;
     constexpr bool FLAG = std::is_same<R, float>::value && !FIXUP;
@@ -136,10 +143,6 @@ void vjp_kernel(const VjpArgs a) {
     __shared__ double sN[EPB][8][9];
     __shared__ double red[7][BLOCK + 1];
     __shared__ int sFlag[EPB];
-    // per lane, across the local update (registers are the limit there): the
-    // frame gradients g^ = Q^T grad N and H, Q
-    __shared__ R sG[EPB][8][25];   // odd row lengths: the lanes spread over the LDS banks
-    __shared__ R sHQ[EPB][8][19];
     const int tid = threadIdx.x;
     const int slot = tid >> 3, gp = tid & 7;
     int32_t cnt_fail = 0, cnt_j0 = 0;
@@ -177,64 +180,31 @@ void vjp_kernel(const VjpArgs a) {
         mat.voce = (VAR & kVarVoceV) ? 1 : 0;
         __syncthreads();
 
-        GPv<R> s;
-        double eps[6];
-        kin_log_v<R, (VAR & kVarFbarV) != 0>(sN[slot], gp, s, eps);
-#pragma unroll
-        for (int I = 0; I < 8; ++I)
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-                sG[slot][gp][3 * I + p] = s.g[I][0] * s.Q[0][p] + s.g[I][1] * s.Q[1][p] + s.g[I][2] * s.Q[2][p];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                sHQ[slot][gp][3 * i + j] = s.H[i][j];
-                sHQ[slot][gp][9 + 3 * i + j] = s.Q[i][j];
-            }
-        asm volatile("" ::: "memory");  // the parked values are re-read, not kept in registers
-        const int64_t oidx = a.orient_pe ? e : 0;
-        if constexpr (ORIENT) {
-            // local update and adjoint in the material frame
-            double Th[3][3];
-            load_rotation(a.orient, oidx, Th);
-            rotate_sym<true>(Th, eps, kSqrt2);
-            rotate_sym<true>(Th, hn, 1.0);
-        }
-        Modes md;
-        hill_modes<true>(mat, md);
-        Local loc;
-        local_update<true>(eps, hn, mat, md, loc);
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                s.H[i][j] = sHQ[slot][gp][3 * i + j];
-                s.Q[i][j] = sHQ[slot][gp][9 + 3 * i + j];
-            }
-        if constexpr (FLAG) {
-            // guard band: the element is recomputed in FP64 (fixup launch)
-            if (valid && fabs(loc.ftr) < 2e-4 * loc.sy_n) sFlag[slot] = 1;
-        }
-        if (valid && !FIXUP) {
-            cnt_fail += loc.converged ? 0 : 1;
-            cnt_j0 += (s.detJ <= R(0)) ? 1 : 0;
-        }
-        double gbar[7] = {0, 0, 0, 0, 0, 0, 0};
-        if (loc.plastic) {
-            // Tbar = P_L : sym(F^T Lambda) in the eigenframe of C
-            const R* gh = sG[slot][gp];  // g^_Iq at 3 I + q
-            R Lh[3][3];  // Lambda^_aq = sum_I lambda_Ia g^_Iq
+        // ---- kinematics, log strain, and the cotangent of the stress
+        // Tbar = P_L : sym(F^T Lambda) (Cartesian Mandel)
+        double eps[6], tb[6];
+        R detJ;
+        {
+            GPv<R> s;
+            kin_log_v<R, (VAR & kVarFbarV) != 0>(sN[slot], gp, s, eps);
+            detJ = s.detJ;
+            R Lh[3][3];  // Lambda^_aq = sum_I lambda_Ia g^_Iq, g^ = Q^T grad N
 #pragma unroll
             for (int i = 0; i < 3; ++i)
 #pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    R v = R(0);
+                for (int p = 0; p < 3; ++p) Lh[i][p] = R(0);
 #pragma unroll
-                    for (int I = 1; I < 8; ++I) v += (R)(sN[slot][I][6 + i] - sN[slot][0][6 + i]) * gh[3 * I + p];
-                    Lh[i][p] = v;
-                }
+            for (int I = 1; I < 8; ++I) {
+                R gh[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    gh[p] = s.g[I][0] * s.Q[0][p] + s.g[I][1] * s.Q[1][p] + s.g[I][2] * s.Q[2][p];
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        Lh[i][p] += (R)(sN[slot][I][6 + i] - sN[slot][0][6 + i]) * gh[p];
+            }
             R fh[3][3];
 #pragma unroll
             for (int i = 0; i < 3; ++i)
@@ -253,9 +223,34 @@ void vjp_kernel(const VjpArgs a) {
                 }
             R tbm[6];
             frame_to_mandel<R>(s.Q, Tb, tbm);
-            double tb[6];
 #pragma unroll
-            for (int k = 0; k < 6; ++k) tb[k] = (double)tbm[k];
+            for (int k = 0; k < 6; ++k) {
+                tb[k] = (double)tbm[k];
+                asm volatile("" : "+v"(tb[k]));  // formed here, not where it is used
+            }
+        }
+        const int64_t oidx = a.orient_pe ? e : 0;
+        if constexpr (ORIENT) {
+            // local update and adjoint in the material frame
+            double Th[3][3];
+            load_rotation(a.orient, oidx, Th);
+            rotate_sym<true>(Th, eps, kSqrt2);
+            rotate_sym<true>(Th, hn, 1.0);
+        }
+        Modes md;
+        hill_modes<true>(mat, md);
+        Local loc;
+        local_update<true>(eps, hn, mat, md, loc);
+        if constexpr (FLAG) {
+            // guard band: the element is recomputed in FP64 (fixup launch)
+            if (valid && fabs(loc.ftr) < 2e-4 * loc.sy_n) sFlag[slot] = 1;
+        }
+        if (valid && !FIXUP) {
+            cnt_fail += loc.converged ? 0 : 1;
+            cnt_j0 += (detJ <= R(0)) ? 1 : 0;
+        }
+        double gbar[7] = {0, 0, 0, 0, 0, 0, 0};
+        if (loc.plastic) {
             if constexpr (ORIENT) {
                 double Th[3][3];
                 load_rotation(a.orient, oidx, Th);
@@ -332,7 +327,7 @@ void vjp_kernel(const VjpArgs a) {
             gbar[4] = uD * d0;
             gbar[5] = uD * d1;
             gbar[6] = uD * d2;
-            const double w = (double)s.detJ;
+            const double w = (double)detJ;
 #pragma unroll
             for (int k = 0; k < 7; ++k) gbar[k] *= w;
         }
