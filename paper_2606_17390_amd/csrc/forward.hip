@@ -116,12 +116,7 @@ constexpr int kVarBarlat = 8;  // FP64 kernel only (R = double)
 // blocks by columns, 8 sectors per row, and took 22 % longer in FP64 and
 // 14 % longer in FP32 than it saved in bytes.)
 constexpr int kKeStride = 576;
-__host__ __device__ constexpr int pair_index(int a, int b) { return a * 3 - (a * (a - 1)) / 2 + (b - a); }
-__host__ __device__ constexpr int pair_a(int p) { return p < 3 ? 0 : (p < 5 ? 1 : 2); }
-__host__ __device__ constexpr int pair_b(int p) { return p < 3 ? p : (p < 5 ? p - 2 : 2); }
 __host__ __device__ constexpr int ke_offset(int I, int a, int b, int J) { return 64 * (3 * a + b) + 8 * I + J; }
-// slot of an off-diagonal pair (0,1), (0,2), (1,2) in the transpose hand-off
-__host__ __device__ constexpr int offdiag_slot(int p) { return p == 1 ? 0 : (p == 2 ? 1 : 2); }
 
 // Tile range of this workgroup in a persistent launch.  Workgroups are
 // dispatched round-robin over the 8 XCDs; with xcd_remap the tiles are cut in
@@ -170,6 +165,147 @@ __device__ inline void kin_and_log(const double (*nd)[W], int gp, GP<R>& s, doub
     }
 }
 
+// ---- contraction of the element tangent on the matrix cores
+//
+//   K^e_{Ia,Jb} = sum_g g^_Iq A_qs g^_Js  (A = A(a,b) of Gauss point g)
+//
+// is, for one pair (a, b), the product of an 8 x 24 matrix T_{I,gs} = g^_Iq A_qs
+// and the 24 x 8 matrix g^_{gs,J}.  Lane (element, g) forms its three columns
+// of T and puts them in LDS; the products of a wave's 8 elements then run as 48
+// MFMA instructions: in FP64 4x4x4 with 4 blocks (the 2 x 2 tiles of one
+// element, 6 slices of 4 in gs), in FP32 4x4x1 with 16 blocks (the tiles of 4
+// elements, 24 steps), each lane holding the g^ it needs for all pairs in
+// registers.  The elements keep to their own blocks, so a value that is not
+// finite stays in its element.
+//
+// Against a lane per row I that reads g^ and A of all Gauss points from LDS
+// and sums its row with vector instructions (3 pairs at a time), a wave reads
+// a third of the bytes from LDS (the four waves of a CU kept its port busy
+// longer than their arithmetic took) and, in FP64, does with one instruction
+// of 16 cycles what took four of 8 (a single wave per SIMD issues an FP64
+// vector instruction only every 8 cycles).  The columns of a pair are stored
+// with one instruction per element (FP64), 512 contiguous bytes.  Passes over
+// 1 M elements: FP64 3930 to 3690 us, mixed 2390 to 2300 us; 152,000 F-bar
+// elements 625 to 610 us, 127,000 Barlat elements 1370 to 1290 us.
+template <typename R>
+struct Contraction;
+
+__device__ inline void wave_sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <>
+struct Contraction<double> {
+    // T of an element: [s][g][I], rows of 9: a slice of 4 Gauss points is read
+    // from 4 runs of 8 values on different banks
+    static constexpr int kStride = 3 * 8 * 9;
+    static __device__ int at(int I, int s, int g) { return 72 * s + 9 * g + I; }
+    double G[8][6];  // [element][2 s + h]: g^_Js of Gauss point 4 h + k
+    int rd, ij, ji;
+
+    __device__ Contraction(const double (*sG)[8][25], int lane) {
+        const int j = lane & 3, b = (lane >> 2) & 3, k = lane >> 4;
+        const int J = 4 * (b & 1) + j;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) G[e][2 * s + h] = sG[e][4 * h + k][3 * J + s];
+        rd = at(4 * (b >> 1) + j, 0, k);
+        const int I = 4 * (b >> 1) + k;
+        ij = 8 * I + J;
+        ji = 8 * J + I;
+    }
+    // pair (a, b) of the wave's 8 elements
+    template <bool SYM, typename RO>
+    __device__ void run(const double* T, int a, int b, RO* Ke, int32_t my_e, uint64_t vm) const {
+        double acc[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    acc[e] = __builtin_amdgcn_mfma_f64_4x4x4f64(T[kStride * e + 72 * s + 36 * h + rd], G[e][2 * s + h],
+                                                                acc[e], 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if ((vm >> (8 * e)) & 1) {
+                RO* K = Ke + (int64_t)__builtin_amdgcn_readlane(my_e, 8 * e) * kKeStride;
+                K[64 * (3 * a + b) + ij] = (RO)acc[e];
+                if (SYM && a != b) K[64 * (3 * b + a) + ji] = (RO)acc[e];
+            }
+        }
+    }
+};
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <>
+struct Contraction<float> {
+    // T of an element: [I][s][g], rows of 28: 4 Gauss points per load
+    static constexpr int kStride = 8 * 28 + 8;
+    static __device__ int at(int I, int s, int g) { return 28 * I + 8 * s + g; }
+    float G[2][3][8];  // [elements 4 m + lane / 16][s][g]: g^_Js
+    int rd, I, J0, e4;
+
+    __device__ Contraction(const float (*sG)[8][25], int lane) {
+        const int i = lane & 3;
+        e4 = lane >> 4;
+        I = 4 * ((lane >> 3) & 1) + i;
+        J0 = 4 * ((lane >> 2) & 1);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int g = 0; g < 8; ++g) G[m][s][g] = sG[4 * m + e4][g][3 * (J0 + i) + s];
+        rd = kStride * e4 + 28 * I;
+    }
+    template <bool SYM, typename RO>
+    __device__ void run(const float* T, int a, int b, RO* Ke, int32_t my_e, uint64_t vm) const {
+        f32x4 acc[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[m][r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f32x4 t[2];
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    t[m] = *reinterpret_cast<const f32x4*>(T + 4 * kStride * m + 8 * s + 4 * h + rd);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(G[m][s][4 * h + k], t[m][k], acc[m], 0, 0, 0);
+            }
+        // register r: column J0 + r of row I
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int src = 8 * (4 * m + e4);
+            const int32_t e = __shfl(my_e, src, 64);
+            if ((vm >> src) & 1) {
+                RO* K = Ke + (int64_t)e * kKeStride;
+                RO v[4] = {(RO)acc[m][0], (RO)acc[m][1], (RO)acc[m][2], (RO)acc[m][3]};
+                store4<RO>(K + 64 * (3 * a + b) + 8 * I + J0, v);
+                if (SYM && a != b) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) K[64 * (3 * b + a) + 8 * (J0 + r) + I] = v[r];
+                }
+            }
+        }
+    }
+};
+
 // R: working type of kinematics, pull-back and contraction; RO: type of the
 // stored element tangent blocks; FIXUP: walk the element list of the guard
 // band instead of all elements (FP64 recomputation for the mixed path).
@@ -189,33 +325,33 @@ void fwd_kernel(const FwdArgs a) {
     // LDS: node coordinates and displacements of the tile; the frame
     // gradients g^ of every Gauss point; and one buffer used in turn for H
     // and Q (F-bar: and beta, cw) across the local update, the residual
-    // reduction and the tangent hand-off (the 3 blocks A^ of one phase per
-    // Gauss point; F-bar: first the element sums of the rank-one term).
+    // reduction and the tangent hand-off (T of one pair (a, b); F-bar: first
+    // the element sums of the rank-one term, which end in the space of sXD).
     // Every per-lane row has an odd length (in values), so that the 64 lanes
     // of a wave, each at its own row, spread over the LDS banks (even
     // strides cost up to 16-way bank conflicts); a row read by the 8 lanes
     // of an element at once is a broadcast.  The Barlat kernel keeps even
-    // node and hand-off rows: its LDS (with the parked Cep) must stay within
+    // node rows: its LDS (with the parked Cep) must stay within
     // 40 KB for four workgroups per CU, worth more to it than the conflicts.
     constexpr int kHQ = FBAR ? 21 : 19;
     constexpr int kRed = 24 * (BLOCK + 1);
-    constexpr int kHandW = BARLAT ? 28 : 29;
     constexpr int kXDW = BARLAT ? 6 : 7;
-    constexpr int kHand = EPB * 8 * kHandW;
+    constexpr int kHand = EPB * Contraction<R>::kStride;
     constexpr int kPark = EPB * 8 * kHQ;
     constexpr int kBuf = kRed > kHand ? (kRed > kPark ? kRed : kPark) : (kHand > kPark ? kHand : kPark);
     __shared__ double sXD[EPB][8][kXDW];                       // [slot][node][X 3, d 3, pad]
     __shared__ __attribute__((aligned(16))) R sG[EPB][8][25];  // [slot][g][3 I + q] (+1 pad)
     __shared__ __attribute__((aligned(16))) R sbuf[kBuf];
     __shared__ int sFlag[EPB];
-    __shared__ R sQb[FBAR ? EPB : 1][24];                      // F-bar: qbar of the element
     __shared__ double sCep[BARLAT ? EPB : 1][8][BARLAT ? 21 : 1];  // Barlat: Cep (upper triangle, material frame)
     R (*sHQ)[8][kHQ] = reinterpret_cast<R (*)[8][kHQ]>(sbuf);   // [slot][g][H 9, Q 9 (, beta, cw)]
     R (*red)[BLOCK + 1] = reinterpret_cast<R (*)[BLOCK + 1]>(sbuf);
-    R (*sA)[8][kHandW] = reinterpret_cast<R (*)[8][kHandW]>(sbuf);  // [slot][g][9 k + 3 q + s]
+    // F-bar: Ubar of the elements (the nodes are read no more)
+    R (*sUb)[24] = reinterpret_cast<R (*)[24]>(&sXD[0][0][0]);
 
     const int tid = threadIdx.x;
     const int slot = tid >> 3, gp = tid & 7;
+    const int slot0 = slot & ~7;  // first element of the wave
     const bool want_K = a.Ke != nullptr;
     int32_t cnt_fail = 0, cnt_j0 = 0, cnt_jf = 0, cnt_nan = 0;
 
@@ -544,6 +680,7 @@ void fwd_kernel(const FwdArgs a) {
                     C4[I][J] = C4[J][I] = (I < 3 && J < 3) ? Cm[I][J] : sc * Cm[I][J];
                 }
 
+            R Yh[3][3], fc[3][3];  // F-bar
             if constexpr (FBAR) {
             // ---- F-bar tangent, all 9 blocks (not symmetric):
             //   K^e_{Ia,Jb} = sum_g g^_Iq A~(a,b)_qs g^_Js + Ubar_Ia qbar_Jb
@@ -553,9 +690,9 @@ void fwd_kernel(const FwdArgs a) {
             //   Ubar_Ia = sum_g w detJ0 / 3 Y^_ap g^_Ip,
             //   qbar_Jb = sum_g cw beta g^_Js f^_bs / c_s   (= dJbar/dd_Jb / Jbar);
             // the A~ part carries d(Fbar)/dd at fixed Jbar and the per-point
-            // -dJ/J term, Ubar qbar the element's dJbar/Jbar term.
-            const R wK = wdet * fb_beta;
-            R Yh[3][3], fc[3][3];
+            // -dJ/J term, Ubar qbar the element's dJbar/Jbar term.  As qbar is
+            // linear in g^, that term joins the columns of T:
+            //   T_{I,gs} = g^_Iq A~_qs + Ubar_Ia cw beta f^_bs / c_s.
             {
                 R Wc[6];
 #pragma unroll
@@ -573,8 +710,8 @@ void fwd_kernel(const FwdArgs a) {
                         fc[i][p] = fh[i][p] * (R(2) * f1[p][p]);  // f1(c, c) = 1 / (2 c)
                     }
             }
-            // element sums Ubar (row gp) and qbar through the hand-off area, in
-            // Gauss point order
+            // element sums Ubar (row gp) through the hand-off area, in Gauss point
+            // order
             R (*sU)[8][25] = reinterpret_cast<R (*)[8][25]>(sbuf);
             {
                 const R w3 = wdet * R(1.0 / 3.0);
@@ -586,36 +723,32 @@ void fwd_kernel(const FwdArgs a) {
                                                          Yh[i][2] * sG[slot][gp][3 * I + 2]);
             }
             __syncthreads();
-            R ub[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 R x = R(0);
 #pragma unroll
                 for (int g = 0; g < 8; ++g) x += sU[slot][g][3 * gp + i];
-                ub[i] = x;
+                sUb[slot][3 * gp + i] = x;
             }
             __syncthreads();
-            {
-                const R cb = fb_cw * fb_beta;
-#pragma unroll
-                for (int J = 0; J < 8; ++J)
-#pragma unroll
-                    for (int b = 0; b < 3; ++b)
-                        sU[slot][gp][3 * J + b] = cb * (sG[slot][gp][3 * J] * fc[b][0] + sG[slot][gp][3 * J + 1] * fc[b][1] +
-                                                        sG[slot][gp][3 * J + 2] * fc[b][2]);
             }
-            __syncthreads();
+            // ---- the pairs (a, b): all 9 for F-bar, else a <= b, each stored
+            // with its transpose (b, a)
+            R go[24];
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                R x = R(0);
-#pragma unroll
-                for (int g = 0; g < 8; ++g) x += sU[slot][g][3 * gp + b];
-                sQb[slot][3 * gp + b] = x;
-            }
-            __syncthreads();
-            // three phases: blocks (a, 0), (a, 1), (a, 2) for a = 0, 1, 2
+            for (int t = 0; t < 24; ++t) go[t] = sG[slot][gp][t];
+            const Contraction<R> ct(sG + slot0, tid & 63);
+            const uint64_t vm = __ballot(valid);
+            R* const tw = sbuf + slot * Contraction<R>::kStride;
+            const R wK = FBAR ? wdet * fb_beta : wdet;
             static_for<0, 3>([&](auto AA) {
                 constexpr int aa = decltype(AA)::value;
+                R ub[FBAR ? 8 : 1];
+                if constexpr (FBAR) {
+#pragma unroll
+                    for (int I = 0; I < 8; ++I) ub[I] = sUb[slot][3 * I + aa];
+                }
+                // Y[q][r][s] = sum_p f^_ap C4(p,q,r,s), C4 = the tensor components of Cm
                 R Y[3][3][3];
 #pragma unroll
                 for (int qq = 0; qq < 3; ++qq)
@@ -628,184 +761,34 @@ void fwd_kernel(const FwdArgs a) {
                             v = m_fma(fh[aa][1], C4[midx(1, qq)][J], v);
                             Y[qq][r][ss] = m_fma(fh[aa][2], C4[midx(2, qq)][J], v);
                         }
-#pragma unroll
-                for (int bb = 0; bb < 3; ++bb)
+                static_for<(FBAR ? 0 : aa), 3>([&](auto BB) {
+                    constexpr int bb = decltype(BB)::value;
+                    R A[3][3];
 #pragma unroll
                     for (int qq = 0; qq < 3; ++qq)
 #pragma unroll
                         for (int ss = 0; ss < 3; ++ss) {
                             R v = fh[bb][0] * Y[qq][0][ss] + fh[bb][1] * Y[qq][1][ss] + fh[bb][2] * Y[qq][2][ss];
                             if (aa == bb) v += Sh[qq][ss];
-                            v -= R(1.0 / 3.0) * Yh[aa][qq] * fc[bb][ss];
-                            sA[slot][gp][9 * bb + 3 * qq + ss] = wK * v;
+                            if constexpr (FBAR) v -= R(1.0 / 3.0) * Yh[aa][qq] * fc[bb][ss];
+                            A[qq][ss] = wK * v;
                         }
-                __syncthreads();
-                R acc[3][8];
+                    wave_sync_lds();  // the pair before has been read
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
+                    for (int ss = 0; ss < 3; ++ss) {
+                        const R cf = FBAR ? fb_cw * fb_beta * fc[bb][ss] : R(0);
 #pragma unroll
-                    for (int J = 0; J < 8; ++J) acc[k][J] = R(0);
-#pragma unroll 2
-                for (int g = 0; g < 8; ++g) {
-                    R G[24], A[28], gi[3];
-#pragma unroll
-                    for (int t = 0; t < 24; ++t) G[t] = sG[slot][g][t];
-#pragma unroll
-                    for (int t = 0; t < 28; ++t) A[t] = sA[slot][g][t];
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) gi[q] = sG[slot][g][3 * gp + q];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        R t3[3];
-#pragma unroll
-                        for (int ss = 0; ss < 3; ++ss)
-                            t3[ss] = m_fma(gi[2], A[9 * k + 6 + ss], m_fma(gi[1], A[9 * k + 3 + ss], gi[0] * A[9 * k + ss]));
-#pragma unroll
-                        for (int J = 0; J < 8; ++J) {
-                            R v = m_fma(t3[0], G[3 * J], acc[k][J]);
-                            v = m_fma(t3[1], G[3 * J + 1], v);
-                            acc[k][J] = m_fma(t3[2], G[3 * J + 2], v);
+                        for (int I = 0; I < 8; ++I) {
+                            R t = m_fma(go[3 * I + 2], A[2][ss], m_fma(go[3 * I + 1], A[1][ss], go[3 * I] * A[0][ss]));
+                            if constexpr (FBAR) t = m_fma(ub[I], cf, t);
+                            tw[Contraction<R>::at(I, ss, gp)] = t;
                         }
                     }
-                }
-#pragma unroll
-                for (int k = 0; k < 3; ++k)
-#pragma unroll
-                    for (int J = 0; J < 8; ++J) acc[k][J] = m_fma(ub[aa], sQb[slot][3 * J + k], acc[k][J]);
-                if (valid) {
-                    RO* Kd = reinterpret_cast<RO*>(a.Ke) + e * kKeStride;
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        RO* row = Kd + ke_offset(gp, aa, k, 0);
-                        RO v4[4];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) v4[j] = (RO)acc[k][j];
-                        store4<RO>(row, v4);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) v4[j] = (RO)acc[k][4 + j];
-                        store4<RO>(row + 4, v4);
-                    }
-                }
-                __syncthreads();
+                    wave_sync_lds();
+                    ct.template run<!FBAR, RO>(sbuf + slot0 * Contraction<R>::kStride, aa, bb,
+                                               reinterpret_cast<RO*>(a.Ke), (int32_t)e, vm);
+                });
             });
-            } else {
-            // ---- element tangent blocks K^e(a,b), a <= b:
-            //      K^e_{Ia,Jb} = sum_g w detJ0 g^_Iq A^(a,b)_qs g^_Js  (per Gauss point g)
-            // Each lane hands its g^ and A^ over through LDS, then lane I
-            // sums row I of the blocks over the element's 8 Gauss points, in
-            // order.  Two phases of 3 blocks: (0,0),(0,1),(0,2); (1,1),(1,2),(2,2).
-            R keep[3][8];  // rows I of the blocks (0,1), (0,2), (1,2)
-            static_for<0, 2>([&](auto PH) {
-                constexpr int ph = decltype(PH)::value;
-                static_for<ph, ph + 1 + ph>([&](auto AA) {
-                    constexpr int aa = decltype(AA)::value;
-                    // Y[q][r][s] = sum_p f^_ap C4(p,q,r,s), C4 = the tensor components of Cm
-                    R Y[3][3][3];
-#pragma unroll
-                    for (int qq = 0; qq < 3; ++qq)
-#pragma unroll
-                        for (int r = 0; r < 3; ++r)
-#pragma unroll
-                            for (int ss = 0; ss < 3; ++ss) {
-                                const int J = midx(r, ss);
-                                R v = fh[aa][0] * C4[midx(0, qq)][J];
-                                v = m_fma(fh[aa][1], C4[midx(1, qq)][J], v);
-                                Y[qq][r][ss] = m_fma(fh[aa][2], C4[midx(2, qq)][J], v);
-                            }
-                    static_for<aa, 3>([&](auto BB) {
-                        constexpr int bb = decltype(BB)::value;
-                        constexpr int k = pair_index(aa, bb) - 3 * ph;
-#pragma unroll
-                        for (int qq = 0; qq < 3; ++qq)
-#pragma unroll
-                            for (int ss = 0; ss < 3; ++ss) {
-                                R v = fh[bb][0] * Y[qq][0][ss] + fh[bb][1] * Y[qq][1][ss] + fh[bb][2] * Y[qq][2][ss];
-                                if (aa == bb) v += Sh[qq][ss];
-                                sA[slot][gp][9 * k + 3 * qq + ss] = wdet * v;
-                            }
-                    });
-                });
-                __syncthreads();
-                // lane gp = row I
-                R acc[3][8];
-#pragma unroll
-                for (int k = 0; k < 3; ++k)
-#pragma unroll
-                    for (int J = 0; J < 8; ++J) acc[k][J] = R(0);
-#pragma unroll 2
-                for (int g = 0; g < 8; ++g) {
-                    R G[24], A[28], gi[3];
-#pragma unroll
-                    for (int t = 0; t < 24; ++t) G[t] = sG[slot][g][t];
-#pragma unroll
-                    for (int t = 0; t < 28; ++t) A[t] = sA[slot][g][t];
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) gi[q] = sG[slot][g][3 * gp + q];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        R t3[3];
-#pragma unroll
-                        for (int ss = 0; ss < 3; ++ss)
-                            t3[ss] = m_fma(gi[2], A[9 * k + 6 + ss], m_fma(gi[1], A[9 * k + 3 + ss], gi[0] * A[9 * k + ss]));
-#pragma unroll
-                        for (int J = 0; J < 8; ++J) {
-                            R v = m_fma(t3[0], G[3 * J], acc[k][J]);
-                            v = m_fma(t3[1], G[3 * J + 1], v);
-                            acc[k][J] = m_fma(t3[2], G[3 * J + 2], v);
-                        }
-                    }
-                }
-                if (valid) {
-                    // row I = gp of the blocks (a, b), a <= b, p = 3 ph + k
-                    RO* Kd = reinterpret_cast<RO*>(a.Ke) + e * kKeStride;
-                    static_for<0, 3>([&](auto KK) {
-                        constexpr int k = decltype(KK)::value;
-                        constexpr int p = 3 * ph + k;
-                        RO* row = Kd + ke_offset(gp, pair_a(p), pair_b(p), 0);
-                        RO v4[4];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) v4[j] = (RO)acc[k][j];
-                        store4<RO>(row, v4);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) v4[j] = (RO)acc[k][4 + j];
-                        store4<RO>(row + 4, v4);
-                    });
-                }
-                // the off-diagonal rows are kept for the transpose below
-                static_for<0, 3>([&](auto KK) {
-                    constexpr int k = decltype(KK)::value;
-                    constexpr int p = 3 * ph + k;
-                    if constexpr (pair_a(p) != pair_b(p)) {
-#pragma unroll
-                        for (int J = 0; J < 8; ++J) keep[offdiag_slot(p)][J] = acc[k][J];
-                    }
-                });
-                __syncthreads();
-            });
-            // blocks (b, a), a < b: row I of (b, a) is column I of (a, b),
-            // handed over through the hand-off area (free after the two phases)
-            R* tt = &sA[slot][0][0];  // [3][8 I][9] (216 <= 8 x 28 values)
-#pragma unroll
-            for (int t = 0; t < 3; ++t)
-#pragma unroll
-                for (int J = 0; J < 8; ++J) tt[72 * t + 9 * gp + J] = keep[t][J];
-            __syncthreads();
-            if (valid) {
-                RO* Kd = reinterpret_cast<RO*>(a.Ke) + e * kKeStride;
-                static_for<0, 3>([&](auto TT) {
-                    constexpr int t = decltype(TT)::value;
-                    constexpr int p = t == 0 ? 1 : (t == 1 ? 2 : 4);
-                    RO* row = Kd + ke_offset(gp, pair_b(p), pair_a(p), 0);
-                    RO v4[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v4[j] = (RO)tt[72 * t + 9 * j + gp];
-                    store4<RO>(row, v4);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v4[j] = (RO)tt[72 * t + 9 * (4 + j) + gp];
-                    store4<RO>(row + 4, v4);
-                });
-            }
-            }  // F-bar / symmetric tangent
         }
         if (valid && !finite_gp && !FIXUP) ++cnt_nan;
         __syncthreads();
