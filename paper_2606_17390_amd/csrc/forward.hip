@@ -306,13 +306,19 @@ struct Contraction<float> {
     }
 };
 
+// The FP64 kernel reads the next tile's node, its values and the history while it
+// works on this one (27 registers): its single wave per SIMD has nothing else to
+// cover the two loads that follow each other.  1 M elements: 3690 to 3530 us, 64 elements: 31.0 to 31.4 us.
+//
 // R: working type of kinematics, pull-back and contraction; RO: type of the
 // stored element tangent blocks; FIXUP: walk the element list of the guard
 // band instead of all elements (FP64 recomputation for the mixed path).
 // The FP32 model variants are held to two waves per SIMD (the plain kernel
 // fits there by itself).  The FP64 kernel runs one wave per SIMD: held to
-// two (at most 256 registers, 20 KB of LDS, only Q parked across the local
-// update) it spilled about 100 registers to scratch and took 10 % longer.
+// two (256 registers, 20 KB of LDS: two columns of Q parked, F Q formed again
+// from d and g^, T one s at a time) it spilled 80 registers to scratch and a
+// pass over 1 M elements took 3950 us against 3690.  Two waves issue an FP64
+// vector instruction every 5.9 cycles, one every 8.1.
 template <typename R, typename RO, int BLOCK, bool FIXUP, int VAR>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(std::is_same<R, float>::value && !FIXUP && VAR != 0 ? 2 : 1)))
 void fwd_kernel(const FwdArgs a) {
@@ -321,6 +327,7 @@ void fwd_kernel(const FwdArgs a) {
     constexpr bool ORIENT = (VAR & kVarOrient) != 0;
     constexpr bool FBAR = (VAR & kVarFbar) != 0;
     constexpr bool BARLAT = (VAR & kVarBarlat) != 0;
+    constexpr bool AHEAD = std::is_same<R, double>::value && !FIXUP && !BARLAT;
     static_assert(!BARLAT || std::is_same<R, double>::value, "the Barlat variant runs in FP64");
     // LDS: node coordinates and displacements of the tile; the frame
     // gradients g^ of every Gauss point; and one buffer used in turn for H
@@ -365,31 +372,50 @@ void fwd_kernel(const FwdArgs a) {
     } else {
         tile_range(a.n_tiles, a.xcd_remap, t0, t1, ts);
     }
-    for (int64_t tile = t0; tile < t1; tile += ts) {
+    auto element_of = [&](int64_t tile) {
         const int64_t e_raw = tile * EPB + slot;
-        const bool valid = e_raw < n_work;
-        int64_t e;
-        if constexpr (FIXUP) e = a.fix_list[valid ? e_raw : 0];
-        else e = valid ? e_raw : (int64_t)a.n_elems - 1;
+        if constexpr (FIXUP) return (int64_t)a.fix_list[e_raw < n_work ? e_raw : 0];
+        else return e_raw < n_work ? e_raw : (int64_t)a.n_elems - 1;
+    };
+    // a lane's node (an out-of-range id is replaced by node 0 and counted, so
+    // no access leaves its buffer), its values and the history
+    int32_t node = 0;
+    double xd[6], hist[7];
+    auto gather = [&](int64_t e) {
+        const int64_t I = (uint32_t)node >= (uint32_t)a.n_nodes ? 0 : node;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            xd[c] = a.X[3 * I + c];
+            xd[3 + c] = a.d[3 * I + c];
+        }
+#pragma unroll
+        for (int k = 0; k < 7; ++k) hist[k] = a.hist_n[k * a.n_gp + e * 8 + gp];
+    };
+    if (AHEAD && t0 < t1) {
+        const int64_t e = element_of(t0);
+        node = a.conn[e * 8 + gp];
+        gather(e);
+    }
+    for (int64_t tile = t0; tile < t1; tile += ts) {
+        const bool valid = tile * EPB + slot < n_work;
+        const int64_t e = element_of(tile);
         const int64_t q = e * 8 + gp;
         if (FLAG && gp == 0) sFlag[slot] = 0;
 
-        // ---- gather (own node through LDS); an out-of-range node id is
-        // replaced by node 0 and counted, so no access leaves its buffer
-        int32_t node = a.conn[q];
-        if ((uint32_t)node >= (uint32_t)a.n_nodes) {
-            if (valid) ++cnt_nan;
-            node = 0;
+        // ---- gather (own node through LDS)
+        if constexpr (!AHEAD) {
+            node = a.conn[q];
+            gather(e);
         }
-        sXD[slot][gp][0] = a.X[3 * (int64_t)node + 0];
-        sXD[slot][gp][1] = a.X[3 * (int64_t)node + 1];
-        sXD[slot][gp][2] = a.X[3 * (int64_t)node + 2];
-        sXD[slot][gp][3] = a.d[3 * (int64_t)node + 0];
-        sXD[slot][gp][4] = a.d[3 * (int64_t)node + 1];
-        sXD[slot][gp][5] = a.d[3 * (int64_t)node + 2];
+        if (valid && (uint32_t)node >= (uint32_t)a.n_nodes) ++cnt_nan;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) sXD[slot][gp][c] = xd[c];
         double hn[7];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) hn[k] = a.hist_n[k * a.n_gp + q];
+        for (int k = 0; k < 7; ++k) hn[k] = hist[k];
+        // (without a branch: with one around the loads the copies behind it wait for them)
+        const int64_t e_next = AHEAD ? element_of(tile + ts < t1 ? tile + ts : tile) : 0;
+        if constexpr (AHEAD) node = a.conn[e_next * 8 + gp];
         Mat mat = load_material(a, e);
         mat.voce = (VAR & kVarVoce) ? 1 : 0;
         __syncthreads();
@@ -420,6 +446,7 @@ void fwd_kernel(const FwdArgs a) {
                 sHQ[slot][gp][9 + 3 * i + j] = s.Q[i][j];
             }
         asm volatile("" ::: "memory");  // the parked values are re-read, not kept in registers
+        if constexpr (AHEAD) gather(e_next);
         const int64_t oidx = a.orient_pe ? e : 0;
         if constexpr (ORIENT) {
             // the local update runs in the material frame
