@@ -488,13 +488,15 @@ extern "C" int fem_history_adjoint(const fem_mesh* mesh, const fem_csr* csr, con
         }
         FEM_HIP_CHECK(launch_hadj_variant(a, var, s));
     }
-    if (g_uniform) {
-        if (ne == 0) FEM_HIP_CHECK(zero_bytes(g_uniform, sizeof(double) * FEM_NGRAD, s));
-        else FEM_HIP_CHECK(reduce_g_uniform(ge, ne, nullptr, 1, g_uniform, s));
-    }
     if (ubar && mesh->n_nodes > 0) {
         if (ne == 0) FEM_HIP_CHECK(zero_bytes(ubar, sizeof(double) * 3 * (size_t)mesh->n_nodes, s));
         else FEM_HIP_CHECK(gather_node_vectors(mesh->n_nodes, csr->node_elem_ptr, csr->node_elem, ue, ubar, s));
+    }
+    if (g_uniform) {
+        // the element vectors have been gathered: their space takes the partial sums
+        if (ne == 0) FEM_HIP_CHECK(zero_bytes(g_uniform, sizeof(double) * FEM_NGRAD, s));
+        else
+            FEM_HIP_CHECK(reduce_g_uniform(ge, ne, nullptr, 1, g_uniform, ue, sizeof(double) * 24 * (size_t)ne, s));
     }
     return FEM_OK;
 }

@@ -76,9 +76,9 @@ hipError_t gather_node_vectors(int32_t n_nodes, const int32_t* ne_ptr, const int
                                double* out, hipStream_t s);
 
 // g_uniform[s][k] = sum over the elements of specimen s of g_elem[k][e]
-// (fixed order; off = NULL for one specimen)
+// (fixed order; off = NULL for one specimen); part: scratch for partial sums
 hipError_t reduce_g_uniform(const double* g_elem, int64_t n_elems, const int64_t* off, int n_spec,
-                            double* g_uniform, hipStream_t s);
+                            double* g_uniform, double* part, size_t part_bytes, hipStream_t s);
 
 // Aggregation multigrid (amg.hip) as fem_solve_amg drives it: numeric
 // set-up for K, then one cycle z = M b per call on stream s (a V-cycle, or

@@ -115,3 +115,27 @@ def test_autograd_function(fem):
     (R2 * lam.reshape(-1)).sum().backward()
     _, ge, _ = oracle.residual_vjp(p.X, p.conn, p.prm, p.d, p.hist_n, p.lam)
     assert np.abs(the.grad.cpu().numpy() - ge).max() <= TOL_FP64 * np.abs(ge).max()
+
+
+@pytest.mark.parametrize("dims,split", [((33, 31, 64), None), ((41, 41, 39), None), ((64, 64, 65), (8, 200000)),
+                                        ((64, 64, 65), (133119,))])
+def test_sum_over_elements(fem, dims, split):
+    """g_uniform is the sum of g_elem over each specimen's elements: in one
+    launch (65,472 elements), from partial sums (65,559), and with specimens of
+    which parts are empty (split: the first elements of the specimens after the
+    first).  A value passes through less than 64 additions, so the bound is
+    64 * 2^-53 of the sum of magnitudes, and that for the reference's own."""
+    p = synth.small_slab(54, *dims, strain=0.01)
+    mesh, params, d, h, bc, lam = gpu_problem(p, fem)
+    off = np.array([0, *(split or ()), p.n_elems], np.int64)
+    batch = fem.Batch(off) if split else None
+    say("sum over elements", p.n_elems, split)
+    v = fem.residual_vjp(mesh, params, d, h, lam, prec=fem.FP64, batch=batch)
+    adj = None if split else fem.history_adjoint(mesh, fem.csr_pattern(mesh), params, d, h, lam=lam)
+    torch.cuda.synchronize()
+    for out in (v,) if split else (v, adj):
+        ge = out.g_elem.cpu().numpy().astype(np.longdouble)
+        gu = out.g_uniform.cpu().numpy().reshape(-1, ge.shape[0])
+        for i in range(len(off) - 1):
+            part = ge[:, off[i]:off[i + 1]]
+            assert np.all(np.abs(gu[i] - part.sum(1)) <= 2 * 64 * 2.0 ** -53 * np.abs(part).sum(1))
