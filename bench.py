@@ -38,17 +38,18 @@ FP64_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 FP32_PEAK_TFLOPS = 2 * FP64_PEAK_TFLOPS
 
 # Counter figures of the element and assembly kernels, taken with rocprofv3 on
-# the 100^3 cube (profiles/): counted VALU flops per Gauss point
-# (SQ_INSTS_VALU_FLOPS_FP32/_FP64/_FP32_TRANS/_FP64_TRANS x 64 lanes / 8e6)
-# and HBM bytes per launch (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the factors of
-# a plain 1 GiB copy).  They hold for the kernel sources whose hash is "sha";
-# once the sources differ they are reported as null.
+# the 100^3 cube (profiles/): counted vector and matrix flops per Gauss point
+# (SQ_INSTS_VALU_FLOPS_FP32/_FP64/_FP32_TRANS/_FP64_TRANS x 64 lanes +
+# SQ_INSTS_VALU_MFMA_MOPS_F64/_F32 x 512, / 8e6) and HBM bytes per launch
+# (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the factors of a plain 1 GiB copy).
+# They hold for the kernel sources whose hash is "sha"; once the sources differ
+# they are reported as null.
 PROFILED = {
-    "sha": "8739b213676c8139",
-    "fp64": {"flop_per_gp": 9155.2,
-             "traffic": {"fwd_kernel": 6.051e9, "assemble_tangent": 6.759e9, "assemble_residual": 3.660e8}},
-    "mixed": {"flop_per_gp": 7516.4,
-              "traffic": {"fwd_kernel": 3.757e9, "assemble_tangent": 3.475e9, "assemble_residual": 3.660e8}},
+    "sha": "b7da9a6ed6b42c28",
+    "fp64": {"flop_per_gp": 7298.3,
+             "traffic": {"fwd_kernel": 6.043e9, "assemble_tangent": 6.760e9, "assemble_residual": 3.661e8}},
+    "mixed": {"flop_per_gp": 7343.4,
+              "traffic": {"fwd_kernel": 3.757e9, "assemble_tangent": 3.475e9, "assemble_residual": 3.662e8}},
 }
 KERNEL_SOURCES = ("paper_2606_17390_amd/csrc/forward.hip", "paper_2606_17390_amd/csrc/fem_device.h",
                   "paper_2606_17390_amd/csrc/barlat.h")

@@ -14,9 +14,9 @@
 //   R^e_Ia  = sum_g w detJ0 P_aA dN_I/dX_A,
 //   K^e_IaJb = sum_g w detJ0 dN_I/dX_A (delta_ab S_AB + F_aC C_CADB F_bD) dN_J/dX_B
 // are formed per Gauss point in the eigenframe (g^ = Q^T grad N, f^ = F Q),
-// summed over the 8 lanes of an element through LDS and stored, with
-// coalesced stores, as the element's 24 residual entries and its 24x24
-// tangent, row by row, in a workspace.
+// summed over the element's Gauss points (the residual through LDS, the
+// tangent on the matrix cores) and stored, with coalesced stores, as the
+// element's 24 residual entries and its 24x24 tangent in a workspace.
 //
 // Assembly (App. E, Alg. E1, without triplets or atomics): the owner of each
 // node gathers, in ascending element order, the blocks of the elements
