@@ -171,6 +171,29 @@ def test_void_specimen_fp64_and_mixed(fem):
     assert rel_inf(gm["K"], o["K"]) <= TOL_MIXED
 
 
+@pytest.mark.parametrize("dims,block", [((7, 1, 1), 64), ((9, 1, 1), 128), ((17, 15, 13), 64), ((17, 15, 13), 256)])
+@pytest.mark.parametrize("fbar", [False, True])
+@pytest.mark.parametrize("prec_name", ["FP64", "FP64_K32", "FP32_MIXED"])
+def test_tile_remainders_and_several_tiles_per_wave(fem, prec_name, fbar, dims, block):
+    """A wave's eight elements and the matrix-core blocks of each, where tiles
+    are not full (7, 9 and 3,315 elements), and waves that take two tiles in
+    turn (3,315 elements on 2,048 slots), the second read ahead in FP64."""
+    p = synth.with_model(synth.small_slab(46, *dims, per_element=True), 47, "swift", fbar, None)
+    prec = getattr(fem, prec_name)
+    cfg_prec = fem.FP32_MIXED if prec_name == "FP32_MIXED" else fem.FP64
+    say("tile remainders", prec_name, fbar, dims, block)
+    o = oracle_forward(p)
+    fem.set_launch(fem.KERNEL_FORWARD, cfg_prec, block=block, waves_per_cu=1)
+    try:
+        g = gpu_forward(p, fem, prec)
+    finally:
+        fem.set_launch(fem.KERNEL_FORWARD, cfg_prec)
+    tol = TOL_MIXED if prec_name == "FP32_MIXED" else TOL_FP64
+    assert rel_inf(g["R"], o["R"], residual_scale(p)) <= tol
+    assert rel_inf(g["K"], o["K"]) <= (TOL_FP64 if prec_name == "FP64" else TOL_MIXED)
+    assert hist_rel(g["hist"], o["hist"]) <= tol
+
+
 def test_residual_only_and_no_bc(fem):
     p = CASES["ragged_7x3x2"]()
     o = oracle_forward(p, bc=False, want_K=False)
