@@ -225,7 +225,13 @@ __global__ __launch_bounds__(256) void bj_minv_kernel(int32_t n, const int32_t* 
 }
 
 // Galerkin block sums: coarse block q = sum over its fine blocks g of the
-// masked 3x3 entries (fixed order, FP64 accumulation, FP32 result).
+// masked 3x3 entries (fixed order, FP64 accumulation, FP32 result).  Bound by
+// the latency of the scattered blocks: the entries of kGalAhead of them are
+// loaded together, whether masked or not (all belong to the matrix), where a
+// load per set bit was waited for before the next.  1,030,000 to 129,000 nodes
+// (FP32): 1900 us, 884 us now (eight together 774 us, but 49 us against 43 us on
+// 6,700 nodes, FP64, 96 us before).
+constexpr int kGalAhead = 4;
 template <typename RV>
 __global__ __launch_bounds__(256) void galerkin_kernel(int64_t nb, const int32_t* __restrict__ gptr,
                                                        const int32_t* __restrict__ goff,
@@ -238,15 +244,26 @@ __global__ __launch_bounds__(256) void galerkin_kernel(int64_t nb, const int32_t
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nb) return;
     double s[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int32_t g = gptr[q]; g < gptr[q + 1]; ++g) {
-        const int64_t off = goff[g];
-        const int32_t len = glen[g];
-        const uint32_t m = gmask[g];
+    const int32_t g1 = gptr[q + 1];
+    for (int32_t g = gptr[q]; g < g1; g += kGalAhead) {
+        int32_t off[kGalAhead], len[kGalAhead];
+        uint32_t m[kGalAhead];
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+        for (int u = 0; u < kGalAhead; ++u) {
+            const int32_t k = g + u < g1 ? g + u : g;
+            off[u] = goff[k];
+            len[u] = glen[k];
+            m[u] = g + u < g1 ? gmask[k] : 0u;
+        }
+        RV v[kGalAhead][9];
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-                if ((m >> (3 * a + c)) & 1u) s[3 * a + c] += (double)fine[off + (int64_t)a * len + c];
+        for (int u = 0; u < kGalAhead; ++u)
+#pragma unroll
+            for (int e = 0; e < 9; ++e) v[u][e] = fine[(int64_t)off[u] + (int64_t)(e / 3) * len[u] + e % 3];
+#pragma unroll
+        for (int u = 0; u < kGalAhead; ++u)
+#pragma unroll
+            for (int e = 0; e < 9; ++e) s[e] += (m[u] >> e) & 1u ? (double)v[u][e] : 0.0;
     }
     const uint32_t fix = gfix[q];
 #pragma unroll
