@@ -70,64 +70,82 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// KT = K^T on the same (structurally symmetric) pattern, one wave per node I.
-// For the r-th neighbour J the block (J, I) is found in J's rows at the slot of
-// I in J's column list: from the pattern's elem_rank through an element that
-// holds both (RANKS; two byte loads), else by a binary search of J's list.
+// KT = K^T on the same (structurally symmetric) pattern, one wave per node I,
+// from row_ptr and col_idx alone.  For the r-th neighbour J the block (J, I) is
+// found in J's rows at the slot of I in J's column list.  Lane r tries the slot
+// that a point-symmetric stencil has (one scattered load; right for 94 % of the
+// blocks of a 100 x 100 x 20 grid, 79 % of a sheet with voids); the lists of
+// the neighbours where it is another are read whole, half a wave per list, by
+// as many loads as there are 32 neighbours in one, and the lane that meets 3I
+// leaves its place in LDS.
 // Lane (r, b) then reads the three entries of row b of that block; the node's
 // rows are put together in LDS and stored coalesced, rows of constrained dofs
 // as identity rows.  Bound by the scattered reads (24 bytes from a row of
 // 648): the workgroups of an XCD take one contiguous eighth of the nodes, so
 // that the five nodes that need a cache line of J's rows find it in one L2.
-// FP64, 213,000 nodes: 663 us with one lane per block, a search per lane and
-// neighbouring nodes on different XCDs; 294 us now (0.41 GB written, 0.41 GB
-// read at the least).  Two rows of blocks per lane in flight, and the loads of
-// the two index chains issued together, measured the same 294 us.
+// FP64, 213,000 nodes: 650 us with one lane per block, a binary search per lane
+// and neighbouring nodes on different XCDs; 323 us now (0.41 GB written, 0.41 GB
+// read at the least; 430 us with every list read whole, 811 against 750 us where
+// the nodes are numbered at random and hardly any first try is right).
 constexpr int kTrWaves = 4;
-constexpr int kTrMax = 64;  // neighbours of a node in a pattern of fem_csr_pattern
+constexpr int kTrMax = 64;   // neighbours of a node in a pattern of fem_csr_pattern
+constexpr int kTrAhead = 4;  // pairs of lists requested together
 
-template <typename RV, bool RANKS>
+template <typename RV>
 __global__ __launch_bounds__(64 * kTrWaves) void transpose_kernel(
     int32_t n_nodes, int64_t n_chunk, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    const uint8_t* __restrict__ elem_rank, const int32_t* __restrict__ ne_ptr, const int32_t* __restrict__ ne_list,
     const RV* __restrict__ K, const uint8_t* __restrict__ bc, RV* __restrict__ KT) {
     __shared__ RV sv[kTrWaves][9 * kTrMax];
     __shared__ int32_t soff[kTrWaves][kTrMax];
     __shared__ int32_t slen[kTrWaves][kTrMax];
+    __shared__ int32_t smiss[kTrWaves][kTrMax];
     const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
     const int64_t I = ((int64_t)(blockIdx.x & 7) * n_chunk + (blockIdx.x >> 3)) * kTrWaves + w;
     if (I >= n_nodes) return;  // the whole wave; no workgroup barrier below
-    const int32_t bI = row_ptr[3 * I], ld = row_ptr[3 * I + 1] - bI;
+    const int32_t bI = row_ptr[3 * I], ld = row_ptr[3 * I + 1] - bI, want = 3 * (int32_t)I;
     const int32_t deg = ld / 3 < kTrMax ? ld / 3 : kTrMax, len = 3 * deg;
     uint32_t bcm = 0;
     if (bc) bcm = (bc[3 * I] ? 1u : 0u) | (bc[3 * I + 1] ? 2u : 0u) | (bc[3 * I + 2] ? 4u : 0u);
     int32_t J = -1, bJ = 0, lenJ = 0;
+    bool found = true;
     if (lane < deg) {
         J = col_idx[bI + 3 * lane] / 3;
         bJ = row_ptr[3 * J];
         lenJ = row_ptr[3 * J + 1] - bJ;
+        // counted from the end of the list: J's for the first half of the
+        // neighbours, I's for the second
+        const int32_t at = max(min((2 * lane < deg ? lenJ : len) - 3 * (lane + 1), lenJ - 3), 0);
+        found = lenJ > 0 && col_idx[bJ + at] == want;
+        soff[w][lane] = found ? bJ + at : bJ;
         slen[w][lane] = lenJ;
     }
     const uint64_t self = __ballot(J == (int32_t)I);
     const int32_t diag = self ? 3 * (__ffsll((unsigned long long)self) - 1) : -1;
-    if constexpr (RANKS) {
-        // lane (k, j): node j of the k-th incident element, I its local node v & 7
-        const int32_t k1 = ne_ptr[I + 1];
-        for (int32_t k = ne_ptr[I] + (lane >> 3); k < k1; k += 8) {
-            const int64_t v = ne_list[k];
-            const int j = lane & 7;
-            soff[w][elem_rank[8 * v + j]] = 3 * (int32_t)elem_rank[8 * (v - (v & 7) + j) + (v & 7)];
-        }
+    const uint64_t miss = __ballot(!found);
+    const int n_miss = __popcll(miss);
+    if (n_miss) {
+        if (!found) smiss[w][__popcll(miss & ((1ull << lane) - 1))] = lane;
         wave_sync();
-        if (lane < deg) soff[w][lane] += bJ;
-    } else if (lane < deg) {
-        int32_t a0 = 0, a1 = lenJ / 3 - 1;
-        while (a0 < a1) {
-            const int32_t mid = (a0 + a1) >> 1;
-            if (col_idx[bJ + 3 * mid] < 3 * I) a0 = mid + 1;
-            else a1 = mid;
+        const int half = lane >> 5, k0 = 3 * (lane & 31);
+        for (int i0 = 0; i0 < n_miss; i0 += 2 * kTrAhead) {
+            int32_t r[kTrAhead], b[kTrAhead], n[kTrAhead], c[kTrAhead];
+#pragma unroll
+            for (int u = 0; u < kTrAhead; ++u) {  // past the last one: a list of none
+                const int i = i0 + 2 * u + half;
+                r[u] = i < n_miss ? smiss[w][i] : 0;
+                b[u] = __shfl(bJ, r[u], 64);
+                n[u] = __shfl(lenJ, r[u], 64);
+                n[u] = i < n_miss ? n[u] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kTrAhead; ++u) c[u] = k0 < n[u] ? col_idx[b[u] + k0] : -1;
+#pragma unroll
+            for (int u = 0; u < kTrAhead; ++u) {
+                if (c[u] == want) soff[w][r[u]] = b[u] + k0;
+                for (int k = k0 + 96; k < n[u]; k += 96)
+                    if (col_idx[b[u] + k] == want) soff[w][r[u]] = b[u] + k;
+            }
         }
-        soff[w][lane] = bJ + 3 * a0;  // present: the pattern is symmetric
     }
     wave_sync();
     for (int t = lane; t < len; t += 64) {
@@ -150,13 +168,8 @@ template <typename RV>
 hipError_t launch_transpose(const fem_csr* csr, const RV* K, const uint8_t* bc, RV* KT, hipStream_t s) {
     const int32_t nn = csr->n_rows / 3;
     const int64_t n_chunk = ((nn + kTrWaves - 1) / kTrWaves + 7) / 8;
-    const dim3 grid((unsigned)(8 * n_chunk)), block(64 * kTrWaves);
-    if (csr->elem_rank && csr->node_elem_ptr && csr->node_elem)
-        hipLaunchKernelGGL((transpose_kernel<RV, true>), grid, block, 0, s, nn, n_chunk, csr->row_ptr, csr->col_idx,
-                           csr->elem_rank, csr->node_elem_ptr, csr->node_elem, K, bc, KT);
-    else
-        hipLaunchKernelGGL((transpose_kernel<RV, false>), grid, block, 0, s, nn, n_chunk, csr->row_ptr, csr->col_idx,
-                           (const uint8_t*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr, K, bc, KT);
+    hipLaunchKernelGGL((transpose_kernel<RV>), dim3((unsigned)(8 * n_chunk)), dim3(64 * kTrWaves), 0, s, nn, n_chunk,
+                       csr->row_ptr, csr->col_idx, K, bc, KT);
     return hipGetLastError();
 }
 

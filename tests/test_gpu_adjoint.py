@@ -100,6 +100,40 @@ def test_transpose_of_a_fan_is_exact(fem, fan, prec_name, ranks):
     assert np.array_equal(B, ref)  # a permutation of the values
 
 
+@pytest.mark.parametrize("prec_name", ["FP64", "FP32_MIXED"])
+@pytest.mark.parametrize("numbering", ["grid", "random"])
+def test_transpose_reads_row_ptr_and_col_idx_only(fem, numbering, prec_name):
+    # the arrays of the assembly hold no slots or elements of this pattern: the
+    # transpose takes the pattern from row_ptr and col_idx, on a grid (most
+    # slots of a node in its neighbours' lists follow from its own) and with
+    # the nodes in random order (hardly any does)
+    X, conn = synth.hex_grid(7, 5, 4)
+    rng = np.random.default_rng(87)
+    if numbering == "random":
+        perm = rng.permutation(X.shape[0])
+        X, conn = X[np.argsort(perm)], perm[conn].astype(np.int32)
+    csr = fem.csr_pattern(fem.Mesh(X, conn))
+    n = csr.n_rows
+    csr = fem.Csr(csr.row_ptr, csr.col_idx, torch.full_like(csr.elem_rank, 255), csr.nnz, n,
+                  torch.full_like(csr.node_elem_ptr, -5), torch.full_like(csr.node_elem, 2**30))
+    real = torch.float64 if prec_name == "FP64" else torch.float32
+    K = torch.as_tensor(rng.standard_normal(csr.nnz)).to("cuda").to(real)
+    bc = torch.as_tensor(rng.random(n) < 0.2).to("cuda").to(torch.uint8)
+    say("transpose without the assembly's arrays", numbering, prec_name, csr.nnz)
+    KT = fem.csr_transpose(csr, K, bc_mask=bc)
+    torch.cuda.synchronize()
+    rp, ci = csr.row_ptr.cpu().numpy(), csr.col_idx.cpu().numpy()
+    rows = np.repeat(np.arange(n), np.diff(rp))
+    A, B = np.zeros((n, n)), np.zeros((n, n))
+    A[rows, ci] = K.double().cpu().numpy()
+    B[rows, ci] = KT.double().cpu().numpy()
+    ref = A.T.copy()
+    m = bc.bool().cpu().numpy()
+    ref[m] = 0.0
+    ref[m, np.nonzero(m)[0]] = 1.0
+    assert np.array_equal(B, ref)  # a permutation of the values
+
+
 MODELS = {"plain": ("swift", False, None), "voce_orient_pe": ("voce", False, "per_element"),
           "fbar": ("swift", True, None), "fbar_voce_orient": ("voce", True, "uniform")}
 
