@@ -468,9 +468,12 @@ __device__ __forceinline__ void local_update_barlat(const double eps[6], const d
         // gn: the scaled residual, stress rows E : G1 over mu, the yield row
         // over sigma_y(alpha_n); converged at 1e-14, or at the rounding floor (a
         // step below 1e-9 that does not halve it; the floor grows with the
-        // stress, so no fixed level detects it)
-        const bool conv = it < 60 && (gn <= 1e-14 || (gn <= 1e-9 && gn >= 0.5 * prev));
-        const bool last = conv || it >= 60 || !(gn == gn);
+        // stress, so no fixed level detects it).  A residual that is not a
+        // number (fmax passes it over, the merit keeps it) ends the iteration
+        // without convergence
+        const bool number = psi == psi;
+        const bool conv = number && it < 60 && (gn <= 1e-14 || (gn <= 1e-9 && gn >= 0.5 * prev));
+        const bool last = conv || it >= 60 || !number;
         prev = gn;
         // the bordered system at the iterate
         double A[6][6], w[6];

@@ -147,3 +147,26 @@ def test_exponents_match_oracle(fem, m):
     assert rel_inf(g["K"], o["K"]) <= TOL_FP64
     assert hist_rel(g["hist"], o["hist"]) <= TOL_FP64
     assert np.array_equal(g["diag"], o["diag"])
+
+
+def test_a_state_without_a_finite_residual_is_not_converged(fem):
+    """Two disjoint cubes under the same stretch: in the first, whose modulus is
+    1e45, the eighth powers of the trial stress overflow and the local residual
+    is not a number, so its Gauss points are reported as not converged and not
+    finite; the second is not touched by it."""
+    Xc, cc = synth.hex_grid(1, 1, 1, 1.0, 1.0, 1.0)
+    X = np.concatenate([Xc, Xc + np.array([2.0, 0.0, 0.0])])
+    conn = np.concatenate([cc, cc + 8]).astype(np.int32)
+    d = np.concatenate([Xc * np.array([0.02, -0.01, -0.009])] * 2)
+    prm = np.stack([synth.params(E=1e45), synth.params()])
+    p = synth.Problem("barlat_overflow", X, conn, d, np.zeros((7, 16)), prm, None, None, barlat=synth.BARLAT_AA6111)
+    say("barlat overflow")
+    g = gpu_forward(p, fem, fem.FP64, bc=False)
+    say("  diag", g["diag"])
+    assert g["diag"][0] == 8 and g["diag"][3] == 8
+    one = synth.Problem("barlat_one", Xc, cc.astype(np.int32), d[8:], np.zeros((7, 8)), prm[1], None, None,
+                        barlat=synth.BARLAT_AA6111)
+    o = oracle_forward(one, bc=False)
+    assert (o["hist"][6] > 0).all() and list(o["diag"]) == [0, 0, 0, 0]
+    assert hist_rel(g["hist"][:, 8:], o["hist"]) <= TOL_FP64
+    assert rel_inf(np.asarray(g["R"]).reshape(-1)[24:], np.asarray(o["R"]).reshape(-1)) <= TOL_FP64
