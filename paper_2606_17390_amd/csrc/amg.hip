@@ -1597,6 +1597,10 @@ bool plan_tail(const std::vector<HostLevel>& H, int t, bool dense, std::vector<H
                 o.plen[g] = 3 * deg;
                 o.pc[g] |= (uint64_t)h.ncol[h.bptr[I] + k] << (16 * j);
             }
+            // the places after the row's last block: zeros times a column of
+            // the row, so that an entry that is not finite reaches no other row
+            for (int32_t k = deg; k > 0 && k % kSeg; ++k)
+                o.pc[first[I] + k / kSeg] |= (uint64_t)h.ncol[h.bptr[I] + deg - 1] << (16 * (k % kSeg));
         }
         if (l == t && ns > kTailSeg0) return false;
         seg_max = std::max(seg_max, (size_t)ns);

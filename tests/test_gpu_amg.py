@@ -450,3 +450,29 @@ def test_fgmres_kcycle_full_size_true_residual(fem):
     assert len(kl) >= 2 and its <= 60
     assert res <= 1e-8 and true <= 1.5e-8
     assert its2 == its and torch.equal(x, x2)
+
+
+def test_a_body_that_is_not_finite_stays_by_itself(fem):
+    """Forty disjoint cubes, whose hierarchy ends in forty nodes without
+    couplings (no dense inverse): a right-hand side that is not a number in one
+    body leaves the cycle's result on the others as it is."""
+    n = 40
+    Xc, cc = synth.hex_grid(1, 1, 1, 1.0, 1.0, 1.0)
+    X = np.concatenate([Xc + np.array([2.0 * i, 0.0, 0.0]) for i in range(n)])
+    conn = np.concatenate([cc + 8 * i for i in range(n)]).astype(np.int32)
+    bc = np.zeros(24 * n, np.uint8)
+    bc.reshape(n, 8, 3)[:, :2] = 1
+    p = synth.Problem("bodies", X, conn, np.zeros_like(X), np.zeros((7, 8 * n)), synth.params(), bc, None)
+    csr, K, bcm = tangent(fem, p, fem.FP64)
+    amg = fem.AMG(csr, K, bcm)
+    amg.update(K)
+    levels, dense = amg.info()
+    say(f"disjoint bodies: levels {levels} dense {dense}")
+    assert [l[0] for l in levels] == [8 * n, n] and not dense
+    r = np.random.default_rng(15).standard_normal(csr.n_rows) * (bc == 0)
+    z = amg.apply(torch.as_tensor(r).cuda())
+    r[23] = np.nan  # a free dof of the first body
+    zn = amg.apply(torch.as_tensor(r).cuda())
+    torch.cuda.synchronize()
+    assert torch.isfinite(z).all() and torch.isnan(zn[23])
+    assert torch.equal(zn[24:], z[24:])
