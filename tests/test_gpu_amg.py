@@ -476,3 +476,148 @@ def test_a_body_that_is_not_finite_stays_by_itself(fem):
     torch.cuda.synchronize()
     assert torch.isfinite(z).all() and torch.isnan(zn[23])
     assert torch.equal(zn[24:], z[24:])
+
+
+def tail_segments(csr, aggs, t):
+    """Segments of four blocks of level t's rows, from the pattern of K and the
+    aggregates."""
+    import scipy.sparse as sp
+    rp, ci = csr.row_ptr.cpu().numpy(), csr.col_idx.cpu().numpy()
+    n = csr.n_rows // 3
+    deg = np.diff(rp)[::3] // 3
+    first = np.repeat(rp[:-1:3], deg) + 3 * (np.arange(deg.sum()) - np.repeat(np.cumsum(deg) - deg, deg))
+    G = sp.csr_matrix((np.ones(deg.sum()), ci[first] // 3, np.concatenate([[0], np.cumsum(deg)])), shape=(n, n))
+    for agg in aggs[:t]:
+        P = sp.csr_matrix((np.ones(agg.size), (np.arange(agg.size), agg)))
+        G = (P.T @ G @ P).tocsr()
+    return int((-(-np.diff(G.indptr) // 4)).sum())
+
+
+@pytest.mark.parametrize("cycle", ["v", "k"])
+def test_tail_too_large_to_be_packed_matches_the_definition(fem, cycle):
+    """A 30^3 cube, whose first level of at most 512 nodes has more than the
+    2,048 segments of four blocks that the packed single-workgroup tail holds:
+    the cycle through the unpacked one equals the numpy cycle."""
+    p = cube_state(30)
+    csr, K, bc = tangent(fem, p, fem.FP64)
+    amg = fem.AMG(csr, K, bc)
+    amg.update(K)
+    amg.set_cycle(cycle, 0 if cycle == "k" else None)
+    levels, dense, omegas = amg.info(omega=True)
+    aggs = [amg.aggregates(l) for l in range(1, len(levels))]
+    t = next(l for l in range(1, len(levels)) if levels[l][0] <= 512)
+    seg = tail_segments(csr, aggs, t)
+    say(f"unpacked tail, {cycle}-cycle: levels {levels}, tail from level {t}, {seg} segments")
+    assert dense and seg > 2048
+    A0 = host_csr(csr, K)
+    free0 = p.bc_mask == 0
+    r = np.random.default_rng(16).standard_normal(csr.n_rows) * free0
+    rt = torch.as_tensor(r).cuda()
+    z, z2 = amg.apply(rt), amg.apply(rt)
+    torch.cuda.synchronize()
+    ref = ref_vcycle(A0, free0, aggs, omegas, r, klevels=k_levels(levels, 0) if cycle == "k" else ())
+    err = np.abs(z.cpu().numpy() - ref).max() / np.abs(ref).max()
+    say(f"  rel err {err:.2e}")
+    assert err <= 2e-6
+    assert torch.equal(z, z2)
+
+
+def device_cycle(row_ptr, col, val, free, aggs, omegas, r, klevels):
+    """ref_vcycle on the device (torch, FP64), for systems too large for the
+    host: the finest operator in CSR form, node blocks of coarse operators
+    summed by key."""
+    def operator(I, J, B, n):
+        # CSR of node blocks B [nb, 3, 3] sorted by (I, J)
+        deg = torch.bincount(I, minlength=n)
+        bp = torch.cat([deg.new_zeros(1), torch.cumsum(deg, 0)])
+        k = torch.arange(I.numel(), device=I.device) - bp[I]
+        at = 9 * bp[I] + 3 * k
+        v = torch.empty(9 * I.numel(), dtype=torch.float64, device=I.device)
+        c = torch.empty(9 * I.numel(), dtype=torch.int64, device=I.device)
+        for a in range(3):
+            for b in range(3):
+                v[at + a * 3 * deg[I] + b] = B[:, a, b]
+                c[at + a * 3 * deg[I] + b] = 3 * J + b
+        rp = (9 * bp[:-1, None] + 3 * deg[:, None] * torch.arange(3, device=I.device)).reshape(-1)
+        return torch.sparse_csr_tensor(torch.cat([rp, 9 * bp[-1:]]), c, v, size=(3 * n, 3 * n))
+
+    def smoother(I, J, B, omega):
+        M = omega * torch.linalg.inv(B[I == J])
+        return lambda x: (M @ x.view(-1, 3, 1)).view(-1)
+
+    n = row_ptr.numel() // 3
+    row_ptr, col = row_ptr.long(), col.long()
+    deg = (row_ptr[1::3] - row_ptr[:-1:3]) // 3
+    I = torch.repeat_interleave(torch.arange(n, device=col.device), deg)
+    base = row_ptr[3 * I] + 3 * (torch.arange(I.numel(), device=col.device) - (row_ptr[:-1:3] // 9)[I])
+    J = col[base] // 3
+    B = torch.stack([val[base + a * 3 * deg[I] + b].double() for a in range(3) for b in range(3)], 1).view(-1, 3, 3)
+    As = [torch.sparse_csr_tensor(row_ptr, col, val.double(), size=(3 * n, 3 * n))]
+    Ms, masks = [smoother(I, J, B, omegas[0])], [free]
+    for l, agg in enumerate(aggs, start=1):
+        nc, m = int(agg.max()) + 1, masks[-1].view(-1, 3).double()
+        B *= m[I][:, :, None] * m[J][:, None, :]
+        key, inv = torch.unique(agg[I] * nc + agg[J], return_inverse=True)
+        B = torch.zeros((key.numel(), 9), dtype=torch.float64, device=B.device).index_add_(0, inv, B.reshape(-1, 9))
+        B = B.view(-1, 3, 3)
+        I, J = key // nc, key % nc
+        mc = torch.zeros((nc, 3), device=B.device).index_add_(0, agg, m.float()) > 0
+        B[I == J] += torch.diag_embed((~mc).double())
+        B = B.float().double()
+        As.append(operator(I, J, B, nc))
+        Ms.append(smoother(I, J, B, omegas[l]))
+        masks.append(mc.view(-1))
+    C = torch.linalg.inv(As[-1].to_dense())
+
+    def cycle(l, b):
+        if l == len(As) - 1:
+            return C @ b
+        x = Ms[l](b)
+        agg, m, nc = aggs[l], masks[l].double(), masks[l + 1].numel() // 3
+        rc = torch.zeros((nc, 3), dtype=torch.float64, device=b.device)
+        rc = rc.index_add_(0, agg, (m * (b - As[l] @ x)).view(-1, 3)).view(-1)
+        if l + 1 in klevels:
+            A = As[l + 1]
+            c1 = cycle(l + 1, rc)
+            v1 = A @ c1
+            vv = v1 @ v1
+            a1 = (v1 @ rc) / vv
+            r2 = rc - a1 * v1
+            c2 = cycle(l + 1, r2)
+            v2 = A @ c2
+            g = (v2 @ v1) / vv
+            a2 = (v2 @ r2) / (v2 @ v2 - g * (v2 @ v1))
+            e = (a1 - a2 * g) * c1 + a2 * c2
+        else:
+            e = cycle(l + 1, rc)
+        x = x + m * e.view(-1, 3)[agg].reshape(-1)
+        return x + Ms[l](b - As[l] @ x)
+
+    return cycle(0, r)
+
+
+@pytest.mark.parametrize("n", [24, 105])
+def test_kcycle_on_the_device_matches_the_definition(fem, n):
+    """The K-cycle against its definition evaluated with torch: on 105^3
+    elements, where the finest level and the first coarse one are so large (more
+    than 131,072 nodes) that the coefficients of their Krylov steps come from
+    kernels of their own, and on 24^3, where every consumer forms them."""
+    p = cube_state(n)
+    csr, K, bc = tangent(fem, p, fem.FP64_K32)
+    amg = fem.AMG(csr, K, bc)
+    amg.update(K)
+    amg.set_cycle("k", 0)
+    levels, dense, omegas = amg.info(omega=True)
+    kl = k_levels(levels, 0)
+    say(f"K-cycle {n}^3 on the device: levels {levels}, Krylov levels {sorted(kl)}")
+    assert dense and 1 in kl and (levels[1][0] > 131072) == (n == 105)
+    aggs = [torch.as_tensor(amg.aggregates(l)).cuda().long() for l in range(1, len(levels))]
+    free = bc == 0
+    r = torch.randn(csr.n_rows, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(17))
+    r *= free
+    z = amg.apply(r)
+    ref = device_cycle(csr.row_ptr, csr.col_idx, K, free, aggs, omegas, r, kl)
+    err = float((z - ref).abs().max() / ref.abs().max())
+    say(f"  rel err {err:.2e}")
+    assert err <= 2e-6
+    assert torch.equal(amg.apply(r), z) and bool((z[~free] == 0).all())
