@@ -434,7 +434,8 @@ struct ResidEpilogue {
     }
 };
 
-template <typename RV, bool STAGED>
+static_assert(kFuseNodes >= kStagedMin, "the levels of resid_kernel take the staged product");
+template <typename RV>
 __global__ __launch_bounds__(256, 4) void resid_kernel(int32_t n, const int32_t* __restrict__ row_ptr,
                                                     const int32_t* __restrict__ ncol, const RV* __restrict__ val,
                                                     const double* __restrict__ x, const double* __restrict__ b,
@@ -442,7 +443,7 @@ __global__ __launch_bounds__(256, 4) void resid_kernel(int32_t n, const int32_t*
                                                     const int32_t* __restrict__ fl) {
     if (stopped(fl)) return;
     ResidEpilogue e{b, mask, r};
-    block_rows<RV, STAGED>(n, row_ptr, ncol, val, x, e);
+    block_rows_staged<RV>(n, row_ptr, ncol, val, x, e);
 }
 
 // cb = P^T r (r zero on constrained dofs), cx = M_c cb; one thread per coarse node
@@ -1824,11 +1825,12 @@ const double* cycle_from(fem_amg* h, int l, const double* bl, double* out, int t
     const Level& F = L[l];
     if (F.n > kFuseNodes) {
         if (l == 0 && h->prec == FEM_FP64)
-            FEM_PRODUCT(resid_kernel, double, product_grid<double>(F.n, kNoCap), F.n, F.row_ptr, F.ncol,
-                        static_cast<const double*>(h->K), F.x, bl, F.mask, F.r, fl);
+            hipLaunchKernelGGL(resid_kernel<double>, dim3(product_grid<double>(F.n, kNoCap)), dim3(256), 0, s, F.n,
+                               F.row_ptr, F.ncol, static_cast<const double*>(h->K), F.x, bl, F.mask, F.r, fl);
         else
-            FEM_PRODUCT(resid_kernel, float, product_grid<float>(F.n, kNoCap), F.n, F.row_ptr, F.ncol,
-                        l == 0 ? static_cast<const float*>(h->K) : (const float*)F.vals, F.x, bl, F.mask, F.r, fl);
+            hipLaunchKernelGGL(resid_kernel<float>, dim3(product_grid<float>(F.n, kNoCap)), dim3(256), 0, s, F.n,
+                               F.row_ptr, F.ncol, l == 0 ? static_cast<const float*>(h->K) : (const float*)F.vals,
+                               F.x, bl, F.mask, F.r, fl);
         hipLaunchKernelGGL(restrict_kernel, dim3(blocks_for(C.n)), dim3(256), 0, s, C.n, C.mptr, C.mem, F.r, C.minv,
                            C.b, C.x, fl);
     } else if (l == 0 && h->prec == FEM_FP64) {

@@ -101,17 +101,9 @@ __device__ inline void static_for(Fn&& f) {
     }
 }
 
-// 4 consecutive values with vector stores (16-byte aligned destination)
-template <typename R>
-__device__ inline void store4(R* p, const R v[4]);
-template <>
-__device__ inline void store4<float>(float* p, const float v[4]) {
+// 4 consecutive values with a vector store (16-byte aligned destination)
+__device__ inline void store4(float* p, const float v[4]) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
-template <>
-__device__ inline void store4<double>(double* p, const double v[4]) {
-    reinterpret_cast<double2*>(p)[0] = make_double2(v[0], v[1]);
-    reinterpret_cast<double2*>(p)[1] = make_double2(v[2], v[3]);
 }
 
 // ---------------------------------------------------------------- kinematics
@@ -124,65 +116,9 @@ __host__ __device__ constexpr int sgz(int I) { return I >= 4 ? 1 : -1; }
 // Shape-function gradients at Gauss point gp, reference Jacobian and the
 // displacement gradient H = grad u (F = I + H is never formed in storage, so
 // that H keeps its relative precision in FP32 at small strains).
-// xs, ds: node coordinates / displacements relative to node 0 (translations
-// drop out of both J0 and grad u because the dN sum to zero).
-template <typename R>
-__device__ inline void kinematics(const R xs[8][3], const R ds[8][3], int gp, R g[8][3], R& detJ,
-                                  R Hd[3][3]) {
-    const R r = R(kInvSqrt3);
-    const R xi = (gp & 1) ? r : -r, eta = (gp & 2) ? r : -r, zeta = (gp & 4) ? r : -r;
-    R dN[8][3];
-#pragma unroll
-    for (int I = 0; I < 8; ++I) {
-        const R a = R(1) + R(sgx(I)) * xi, b = R(1) + R(sgy(I)) * eta, c = R(1) + R(sgz(I)) * zeta;
-        dN[I][0] = R(0.125) * R(sgx(I)) * b * c;
-        dN[I][1] = R(0.125) * a * R(sgy(I)) * c;
-        dN[I][2] = R(0.125) * a * b * R(sgz(I));
-    }
-    R J[3][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            R s = R(0);
-#pragma unroll
-            for (int I = 1; I < 8; ++I) s += xs[I][i] * dN[I][j];
-            J[i][j] = s;
-        }
-    const R c00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-    const R c01 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-    const R c02 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-    detJ = J[0][0] * c00 + J[0][1] * c01 + J[0][2] * c02;
-    const R id = inv_det(detJ);
-    // Jinv[j][A]
-    R Ji[3][3];
-    Ji[0][0] = c00 * id;
-    Ji[1][0] = c01 * id;
-    Ji[2][0] = c02 * id;
-    Ji[0][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
-    Ji[1][1] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
-    Ji[2][1] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
-    Ji[0][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
-    Ji[1][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
-    Ji[2][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
-#pragma unroll
-    for (int I = 0; I < 8; ++I)
-#pragma unroll
-        for (int A = 0; A < 3; ++A) g[I][A] = Ji[0][A] * dN[I][0] + Ji[1][A] * dN[I][1] + Ji[2][A] * dN[I][2];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int A = 0; A < 3; ++A) {
-            R s = R(0);
-#pragma unroll
-            for (int I = 1; I < 8; ++I) s += ds[I][a] * g[I][A];
-            Hd[a][A] = s;
-        }
-}
-
-// Same as kinematics(), reading the element's node coordinates and
-// displacements (nd[I][0..2] = X_I, nd[I][3..5] = d_I, FP64 in LDS) as they
-// are needed, relative to node 0.
+// nd[I][0..2] = X_I, nd[I][3..5] = d_I (FP64 in LDS), read as they are needed,
+// relative to node 0 (translations drop out of both J0 and grad u because the
+// dN sum to zero).
 template <typename R, int W>
 __device__ inline void kinematics_lds(const double (*nd)[W], int gp, R g[8][3], R& detJ, R Hd[3][3]) {
     const R r = R(kInvSqrt3);

@@ -296,7 +296,7 @@ struct Contraction<float> {
             if ((vm >> src) & 1) {
                 RO* K = Ke + (int64_t)e * kKeStride;
                 RO v[4] = {(RO)acc[m][0], (RO)acc[m][1], (RO)acc[m][2], (RO)acc[m][3]};
-                store4<RO>(K + 64 * (3 * a + b) + 8 * I + J0, v);
+                store4(K + 64 * (3 * a + b) + 8 * I + J0, v);
                 if (SYM && a != b) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) K[64 * (3 * b + a) + 8 * (J0 + r) + I] = v[r];
