@@ -56,6 +56,14 @@ struct WsCounter {
     }
 };
 
+// Orders a wave's LDS stores before loads of the same addresses by other
+// lanes of that wave.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Zero `bytes` bytes at p on stream s with a kernel (no memset node, so a
 // captured graph may replay it).
 hipError_t zero_bytes(void* p, size_t bytes, hipStream_t s);

@@ -190,12 +190,6 @@ __device__ inline void kin_and_log(const double (*nd)[W], int gp, GP<R>& s, doub
 template <typename R>
 struct Contraction;
 
-__device__ inline void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <>
 struct Contraction<double> {
     // T of an element: [s][g][I], rows of 9: a slice of 4 Gauss points is read
@@ -800,7 +794,7 @@ void fwd_kernel(const FwdArgs a) {
                             if constexpr (FBAR) v -= R(1.0 / 3.0) * Yh[aa][qq] * fc[bb][ss];
                             A[qq][ss] = wK * v;
                         }
-                    wave_sync_lds();  // the pair before has been read
+                    wave_sync();  // the pair before has been read
 #pragma unroll
                     for (int ss = 0; ss < 3; ++ss) {
                         const R cf = FBAR ? fb_cw * fb_beta * fc[bb][ss] : R(0);
@@ -811,7 +805,7 @@ void fwd_kernel(const FwdArgs a) {
                             tw[Contraction<R>::at(I, ss, gp)] = t;
                         }
                     }
-                    wave_sync_lds();
+                    wave_sync();
                     ct.template run<!FBAR, RO>(sbuf + slot0 * Contraction<R>::kStride, aa, bb,
                                                reinterpret_cast<RO*>(a.Ke), (int32_t)e, vm);
                 });
@@ -876,14 +870,6 @@ __global__ __launch_bounds__(kResThreads) void assemble_residual(
         }
         if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
     }
-}
-
-// Orders a wave's LDS stores before loads of the same addresses by other
-// lanes of that wave.
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 constexpr int kTanWaves = 4;  // nodes (waves) per workgroup of assemble_tangent

@@ -132,12 +132,6 @@ __device__ int node_neighbours(int32_t n, const int32_t* __restrict__ conn, cons
 constexpr int kPatWaves = 4;  // waves per workgroup
 constexpr int kNodes = 8;     // nodes per wave
 
-__device__ inline void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int CTRL>
 __device__ inline uint32_t dpp(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);
@@ -270,7 +264,7 @@ __global__ __launch_bounds__(64 * kPatWaves) void node_pass(
                 if (u < 3 * len) row[u] = scol[w][u - (u >= len ? len : 0) - (u >= 2 * len ? len : 0)];
             }
         }
-        wave_sync_lds();
+        wave_sync();
     };
 
     int32_t my_deg = 0;  // lane t: of node n0 + t
@@ -298,7 +292,7 @@ __global__ __launch_bounds__(64 * kPatWaves) void node_pass(
 #pragma unroll
                 for (int b = 0; b < 3; ++b) scol[w][3 * below + b] = 3 * (int32_t)x + b;
             }
-            wave_sync_lds();
+            wave_sync();
             const int32_t e = __builtin_amdgcn_ds_bpermute((8 * t + m) << 2, entry);
             if (e != INT32_MAX) {
                 const int32_t v = (int32_t)own;
@@ -317,14 +311,14 @@ __global__ __launch_bounds__(64 * kPatWaves) void node_pass(
         const int64_t k0t = inc_ptr[n0 + t], k1t = inc_ptr[n0 + t + 1];
         int s = 0;
         if (lane == 0) s = node_neighbours((int32_t)(n0 + t), conn, inc_ptr, inc, snb[w]);
-        wave_sync_lds();
+        wave_sync();
         const int deg = __builtin_amdgcn_readfirstlane(s);
         if (lane == t) my_deg = deg;
         if constexpr (FILL) {
             if (deg <= 0) continue;  // reported by the counting call
             if (lane < deg)
                 for (int b = 0; b < 3; ++b) scol[w][3 * lane + b] = 3 * snb[w][lane] + b;
-            wave_sync_lds();
+            wave_sync();
             for (int64_t k = k0t + m; k < k1t; k += 8) {
                 const int32_t e = inc[k];
                 const int32_t v = conn[(int64_t)(e & ~7) + q];

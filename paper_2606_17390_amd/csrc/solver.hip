@@ -62,14 +62,6 @@ __global__ __launch_bounds__(256) void spmv_kernel(int32_t n_nodes, const int32_
     if (node < n_nodes && l < 3) y[3 * node + l] = (l == 0 ? s0 : (l == 1 ? s1 : s2));
 }
 
-// Orders a wave's LDS stores before loads of the same addresses by other
-// lanes of that wave.
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // KT = K^T on the same (structurally symmetric) pattern, one wave per node I,
 // from row_ptr and col_idx alone.  For the r-th neighbour J the block (J, I) is
 // found in J's rows at the slot of I in J's column list.  Lane r tries the slot
