@@ -362,8 +362,9 @@ int fem_solve(const fem_csr *csr, const void *K_vals, fem_precision prec, fem_kr
 
 /*
  * fem_csr_transpose -- KT_vals = values of K^T on the same pattern (the
- * pattern of fem_csr_pattern is structurally symmetric), the matrix of the
- * adjoint solve of Alg. 1 / Eq. (dR_u).  If bc_mask (device [n_rows], may be
+ * pattern of fem_csr_pattern is structurally symmetric; of csr only row_ptr
+ * and col_idx are read), the matrix of the adjoint solve of Alg. 1 /
+ * Eq. (dR_u).  If bc_mask (device [n_rows], may be
  * NULL) marks a dof, row i of KT becomes an identity row, so that solving
  * KT lambda = v with v_i = 0 there gives lambda_i = 0 and the free-free block
  * of K^T for the rest (for a K whose constrained rows are identity rows).

@@ -113,8 +113,8 @@ __device__ inline void reverse_plastic(const Modes& md, const Local& loc, double
 // hold 20 KB of LDS and a lane 256 registers, so the sums over an element's
 // Gauss points reuse the space of the nodes, eight rows at a time, and that of
 // the gradients they are formed from.  Oriented F-bar, 202,000 elements: 320 us
-// with one wave per SIMD (31 KB of LDS, 268 registers), 250 us now (8 to 20
-// registers spilled).
+// with one wave per SIMD (31 KB of LDS, 268 registers), 250 us now (10 to 13
+// registers spilled in the oriented F-bar variants, 0 to 2 in the others).
 template <int VAR>
 __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(2))) void hadj_kernel(const AdjArgs a) {
     constexpr bool ORIENT = (VAR & kVarOrientA) != 0;

@@ -407,7 +407,9 @@ __device__ inline R dd2_triple(R m0, R m1, R m2, R f01, R f02, R f12) {
 // the general forms need a logarithm, a sinh, a square root and six
 // divisions for them.
 constexpr double kAtanhMax = 0.2;
-__device__ inline double atanh_series(double w) {  // w <= 0.04: to 1e-17
+// S to 5e-16 for w <= 0.04: w S, which enters the logarithm and f1, to 2e-17,
+// and f2 through u (1 + |u|) S to 1e-16
+__device__ inline double atanh_series(double w) {
     double s = 1.0 / 21.0;
     s = m_fma(s, w, 1.0 / 19.0);
     s = m_fma(s, w, 1.0 / 17.0);
@@ -556,8 +558,11 @@ struct Modes {
 };
 
 // FAST: quotients and roots from the refined reciprocals.  The FP32-mixed
-// kernels keep the quotients: their results are rounded to float next, and a
-// last-bit change here would move some of those roundings.
+// forward kernel is the one that does not take it (nor the shorter local
+// update below): it still runs as it was first written.  Measured with FAST it
+// gains (pass over 1 M elements 2330 -> 2250 us, 1.25 M elements in 64 batches
+// 4150 -> 4060 us, 6,400 elements 66.6 -> 64.7 us), with the same errors against
+// 64 bits.  The mixed VJP takes FAST.
 template <bool FAST>
 __device__ inline void hill_modes(const Mat& m, Modes& h) {
     if constexpr (FAST) {
@@ -640,15 +645,15 @@ struct Local {
 // phi(lambda) - sigma_y(alpha_n + lambda phi(lambda)) = 0 is solved by a
 // bracketed Newton iteration.
 //
-// FAST (the FP64 kernels) skips two of the evaluations of that condition,
-// each with the hardening law's logarithm and exponential: the one at
-// lambda = 0, whose values are those of the yield check, and the one at the
-// final lambda when the iteration ended on the residual test and so has just
-// made it.  A wave pays for the largest count among its lanes: four
-// evaluations instead of six at an ordinary increment.  With the spectral
-// functions above (divisions and library logarithms out), on the 100^3 cube:
-// FP64 pass 4.39 -> 3.99 ms; FP64 parameter VJP of 60,000 elements 122 -> 93 us;
-// one FP64 pass over 64 elements 36.8 -> 31.6 us.
+// FAST (every kernel but the FP32-mixed forward one) skips two of the
+// evaluations of that condition, each with the hardening law's logarithm and
+// exponential: the one at lambda = 0, whose values are those of the yield
+// check, and the one at the final lambda when the iteration ended on the
+// residual test and so has just made it.  A wave pays for the largest count
+// among its lanes: four evaluations instead of six at an ordinary increment.
+// With the spectral functions above (divisions and library logarithms out), on
+// the 100^3 cube: FP64 pass 4.39 -> 3.99 ms; FP64 parameter VJP of 60,000
+// elements 122 -> 93 us; one FP64 pass over 64 elements 36.8 -> 31.6 us.
 template <bool FAST>
 __device__ inline void local_update(const double eps[6], const double* hist_n, const Mat& m,
                                     const Modes& h, Local& o) {

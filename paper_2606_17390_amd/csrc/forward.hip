@@ -328,10 +328,12 @@ void fwd_kernel(const FwdArgs a) {
     // and Q (F-bar: and beta, cw) across the local update, the residual
     // reduction and the tangent hand-off (T of one pair (a, b); F-bar: first
     // the element sums of the rank-one term, which end in the space of sXD).
-    // Every per-lane row has an odd length (in values), so that the 64 lanes
-    // of a wave, each at its own row, spread over the LDS banks (even
-    // strides cost up to 16-way bank conflicts); a row read by the 8 lanes
-    // of an element at once is a broadcast.  The Barlat kernel keeps even
+    // Every per-lane row but those of T has an odd length (in values), so that
+    // the 64 lanes of a wave, each at its own row, spread over the LDS banks
+    // (even strides cost up to 16-way bank conflicts); a row read by the 8 lanes
+    // of an element at once is a broadcast.  T in FP32 has rows of 28, for
+    // 16-byte loads, and conflicts: 140,000 cycles on each CU of the 3.2 million
+    // that 1 M elements take.  The Barlat kernel keeps even
     // node rows: its LDS (with the parked Cep) must stay within
     // 40 KB for four workgroups per CU, worth more to it than the conflicts.
     constexpr int kHQ = FBAR ? 21 : 19;

@@ -646,8 +646,9 @@ inline int gs_blocks(int64_t n) {
     return (int)std::min<int64_t>(kGrid, (n + piece - 1) / piece);
 }
 // Up to this many workgroups the update sums their partial products itself
-// (31 x 128 values per workgroup at most), which saves a launch; above, a
-// kernel of its own does (4.7 us against 16 MB and more of re-reads).
+// (30 x 128 values per workgroup at most), which saves a launch; above, a
+// kernel of its own does (4.7 us against 4 MB of re-reads by 129 workgroups,
+// which grow with the square of their number).
 constexpr int kGsFuse = 128;
 
 // hpart[i][block] = partial of (w, v_i), i = 0..j.  Bound by HBM on a large

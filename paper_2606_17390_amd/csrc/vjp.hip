@@ -132,8 +132,13 @@ __device__ inline void kin_log_v(const double (*nd)[9], int gp, GPv<R>& s, doubl
 // them: the cotangent of the stress is six numbers formed from the kinematics
 // before the local update, so no gradient, H or Q has to be kept across it, and
 // the constants of the element loop are not hoisted out of it (build flag).
+// The FP64 form still spills 25 to 32 of them (120 to 152 bytes of scratch per
+// lane), the FP32 form none.
 // 60,000 elements, FP64: 80 us with one wave and 23 KB of parked values per
-// wave, 70 us now; 1.2 M elements, mixed: 1190 us to 1110 us.
+// wave, 70 us now; 1.2 M elements, mixed: 1190 us to 1110 us.  A point that
+// stays elastic pays for the cotangent too: where every one does, the mixed call
+// takes 54 us for 60,000 elements, 52 us when the plastic points alone formed it
+// (FP64 77 -> 63 us all the same).
 template <typename R, int BLOCK, bool FIXUP, int VAR>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
 void vjp_kernel(const VjpArgs a) {
